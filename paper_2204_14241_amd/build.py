@@ -5,13 +5,16 @@ Usage: python -m paper_2204_14241_amd.build   (or build_library() from Python)
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhmc.so")
-SOURCES = [os.path.join(CSRC, "hmc.hip")]
-DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("kernels.h", "lattice.h", "fft.h", "precond.h", "metric.h", "probe.h", "march.h")] + [
+SOURCES = [os.path.join(CSRC, f) for f in ("hmc.hip", "fft_f32.hip", "fft_f64.hip", "fft_metric.hip")]
+DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("kernels.h", "lattice.h", "fft.h", "fft_kernels.h", "precond.h", "metric.h",
+                                                  "probe.h", "march.h")] + [
     os.path.join(ROOT, "include", f) for f in ("hmc.h", "hmc_testing.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -22,7 +25,6 @@ FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     "-Wall",
     # keep packed FP32 instructions out of the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -42,10 +44,7 @@ def source_hash():
     return h.hexdigest()[:16]
 
 
-def build_library(verbose=False):
-    """Compile every HIP source into paper_2204_14241_amd/libhmc.so (always rebuilds)."""
-    tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, f'-DHMC_SOURCE_HASH="{source_hash()}"', *SOURCES, "-o", tmp]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -55,6 +54,20 @@ def build_library(verbose=False):
         raise RuntimeError(f"hipcc failed ({res.returncode}):\n{out}")
     if verbose and out.strip():
         print(out)
+
+
+def build_library(verbose=False):
+    """Compile every HIP source (side by side) and link paper_2204_14241_amd/libhmc.so (always
+    rebuilds)."""
+    tmp = LIB + ".tmp"
+    with tempfile.TemporaryDirectory() as d:
+        objs = [os.path.join(d, os.path.basename(s) + ".o") for s in SOURCES]
+        with ThreadPoolExecutor(len(SOURCES)) as pool:
+            jobs = [pool.submit(_run, [HIPCC, *FLAGS, f'-DHMC_SOURCE_HASH="{source_hash()}"', "-c", s, "-o", o], verbose)
+                    for s, o in zip(SOURCES, objs)]
+            for j in jobs:
+                j.result()
+        _run([HIPCC, f"--offload-arch={ARCH}", "-shared", *objs, "-o", tmp], verbose)
     os.replace(tmp, LIB)
     return LIB
 

@@ -29,6 +29,7 @@
 #include "../../include/hmc.h"
 #include "../../include/hmc_testing.h"
 #include "fft.h"
+#include "fft_kernels.h"
 #include "kernels.h"
 #include "precond.h"
 #include "metric.h"
@@ -111,7 +112,8 @@ struct BatchInfo {
     std::vector<long long> sp_off;    // nchains + 1 prefix offsets (complex) of the spinor blocks
     std::vector<int> cfirst;          // nchains + 1 prefix of 256-site tiles (site kernels)
     std::vector<long long> pcoff;     // nchains + 1 prefix offsets (doubles) of preconditioner tables
-    int nslices = 0;                  // sum over units of 4 L_tau (preconditioner slice workgroups)
+    // workgroups (sum over units) and threads of the preconditioner's slice passes [FP64, FP32]
+    int nslices[2] = {0, 0}, xy_threads[2] = {64, 64};
     int ngroups[2] = {0, 0};          // sum over units of the tau-pass workgroups [FP64, FP32]
     // device tables in the workspace; index 0: FP64 launch shape, 1: mixed precision
     UnitDesc* units[2] = {nullptr, nullptr};
@@ -125,7 +127,8 @@ struct BatchInfo {
     int mthreads[2] = {0, 0}, rthreads[2] = {0, 0};
     size_t mlds[2] = {0, 0}, rlds[2] = {0, 0};
     std::vector<UnitDesc> hunits[2];  // host copies of the unit tables
-    int2* pxy_blocks = nullptr;       // preconditioner slice passes: (unit, slice)
+    // preconditioner slice passes: (unit, group of slices) [FP64, FP32]
+    int2* pxy_blocks[2] = {nullptr, nullptr};
     int2* pt_blocks[2] = {nullptr, nullptr};   // tau pass: (unit, column group) [FP64, FP32]
     ChainDesc* chains = nullptr;
     int2* cblocks = nullptr;
@@ -172,7 +175,9 @@ struct hmc_ctx {
     int pc_q[2] = {0, 0};      // chunks per column of the tau pass [FP64, FP32]
     bool pc_full[2] = {false, false};   // every lattice's columns are pc_q full chunks
     long long blob_doubles = 0;    // preconditioner tables of all lattices
-    bool pc_r7 = false;            // some lattice extent needs radix-7 FFT stages
+    // an L (pc_wide) or an N_tau (mt_wide) needs an FFT radix above kFftNarrow
+    bool pc_wide = false, mt_wide = false;
+    SliceCut mt_cut{};             // slice passes of the metric: one slice per workgroup
     // Fourier-diagonal HMC metric (one lattice): the caller's sigma table (null: identity,
     // plain drift and kinetic energy), whether this lattice supports the metric passes, their
     // tau-pass LDS and per-workgroup partial sums
@@ -318,6 +323,8 @@ static std::vector<double> pc_table_blob(const FftPlan& pl, const FftPlan& pt) {
         v[size_t(b.twT + 2 * j)] = w.x;
         v[size_t(b.twT + 2 * j + 1)] = w.y;
     }
+    std::memcpy(&v[size_t(b.planL)], &pl, sizeof(pl));
+    std::memcpy(&v[size_t(b.planT)], &pt, sizeof(pt));
     return v;
 }
 
@@ -421,7 +428,7 @@ static size_t ws_layout(hmc_ctx* c, char* base) {
     char* mp = c->is_batch ? nullptr : take(sizeof(double) * 3 * size_t(std::max(pc_groups(c->lat.LL, pc_ncol<double>()), 256)));
     char* pw = c->is_batch ? nullptr : take(3 * PS * sizeof(double));
     char *un0 = nullptr, *un1 = nullptr, *bl0 = nullptr, *bl1 = nullptr, *ch = nullptr,
-         *cb = nullptr, *cf = nullptr, *cs = nullptr, *pxy = nullptr, *pt0 = nullptr, *pt1 = nullptr,
+         *cb = nullptr, *cf = nullptr, *cs = nullptr, *pxy0 = nullptr, *pxy1 = nullptr, *pt0 = nullptr, *pt1 = nullptr,
          *mb0 = nullptr, *mb1 = nullptr, *rb0 = nullptr, *rb1 = nullptr;
     if (c->is_batch) {
         const size_t nch = size_t(c->bi.nchains);
@@ -433,7 +440,8 @@ static size_t ws_layout(hmc_ctx* c, char* base) {
         cb = take(sizeof(int2) * size_t(c->ngblk));
         cf = take(sizeof(int) * (nch + 1));
         cs = take(sizeof(double) * kChainSlots * nch);
-        pxy = take(sizeof(int2) * size_t(c->bi.nslices));
+        pxy0 = take(sizeof(int2) * size_t(c->bi.nslices[0]));
+        pxy1 = take(sizeof(int2) * size_t(c->bi.nslices[1]));
         pt0 = take(sizeof(int2) * size_t(c->bi.ngroups[0]));
         pt1 = take(sizeof(int2) * size_t(c->bi.ngroups[1]));
         mb0 = take(sizeof(int2) * size_t(c->pslots));
@@ -474,7 +482,8 @@ static size_t ws_layout(hmc_ctx* c, char* base) {
             c->bi.cblocks = reinterpret_cast<int2*>(cb);
             c->bi.cfirst_dev = reinterpret_cast<int*>(cf);
             c->bi.cslots = reinterpret_cast<double*>(cs);
-            c->bi.pxy_blocks = reinterpret_cast<int2*>(pxy);
+            c->bi.pxy_blocks[0] = reinterpret_cast<int2*>(pxy0);
+            c->bi.pxy_blocks[1] = reinterpret_cast<int2*>(pxy1);
             c->bi.pt_blocks[0] = reinterpret_cast<int2*>(pt0);
             c->bi.pt_blocks[1] = reinterpret_cast<int2*>(pt1);
             c->bi.mblocks[0] = reinterpret_cast<int2*>(mb0);
@@ -520,6 +529,37 @@ static MarchPlan batch_march_plan(const Lat& l, int rows, int seg, bool f32, int
     return mp;
 }
 
+// Row pitch of ns slices' working copies in LDS: L + 1 (see fft_slices), or L where only that fits.
+template <typename R>
+static int slice_pitch(int L, int ns) {
+    return (size_t(ns) * L * (L + 1) + L) * sizeof(C2<R>) <= kPcLdsMost ? L + 1 : L;
+}
+// Slices per workgroup of the preconditioner's slice passes over `slices` slices of L x L: small
+// slices are taken together up to kSliceGroup elements (a 48 x 48 slice), so that a workgroup has a
+// butterfly for every thread of a few wavefronts, while two workgroups per CU remain.  The time
+// is flat around the rule: 16 x 16 x 80 with four vectors takes 6.4-7.1 us at 320, 640 and 1280
+// workgroups.  The results do not depend on it.
+constexpr int kSliceGroup = 2304, kSliceWgs = 512;
+template <typename R>
+static SliceCut slice_cut(int L, long long slices) {
+    const long long fit = kSliceGroup / (L * L), spread = slices / kSliceWgs;
+    const int spw = int(std::max(1LL, std::min(fit, spread)));
+    return SliceCut{spw, slice_pitch<R>(L, spw)};
+}
+template <typename R>
+static size_t slice_lds(const SliceCut& sc, int L) {
+    return (size_t(sc.spw) * L * sc.pitch + L) * sizeof(C2<R>);
+}
+// Threads of a slice-pass workgroup: one per butterfly of the stage with most of them, up to
+// kPcBlock.
+static int slice_threads(const SliceCut& sc, int L) {
+    FftPlan p;
+    if (!make_fft_plan(L, p)) return kPcBlock;
+    int r = kFftMaxRadix;
+    for (int i = 0; i < p.nst; ++i) r = std::min(r, p.st[i].radix);
+    return std::min(kPcBlock, (sc.spw * L * (L / r) + 63) / 64 * 64);
+}
+
 // Batch: (re)write the unit and block tables of one precision's launch shape, with the march
 // cuts of step A (this precision) and of the reliable update (FP64).
 static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
@@ -543,6 +583,7 @@ static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
             part += unit_slots(lat);
             d.chain = ch;
             d.pcoff = int(b.pcoff[size_t(ch)]);
+            d.sc = pi ? slice_cut<float>(lat.L, 1LL << 40) : slice_cut<double>(lat.L, 1LL << 40);
             for (int w = 0; w < d.bpr; ++w) blocks.push_back(make_int2(u, w));
             int th = 0;
             size_t lds = 0;
@@ -688,7 +729,7 @@ static void tune_cache_store(const std::string& key, const TuneChoice& c) {
 // --------------------------------------------------------------------------------------
 // geometry of a launch
 
-static GeoOne geo_one(const hmc_ctx* c, int bpr) { return GeoOne{c->lat, bpr, bpr, c->pstride}; }
+static GeoOne geo_one(const hmc_ctx* c, int bpr) { return GeoOne{c->lat, bpr, bpr, c->pstride, SliceCut{}}; }
 static GeoBatch geo_batch(const hmc_ctx* c, int pi) { return GeoBatch{c->bi.units[pi], c->bi.blocks[pi]}; }
 static CGeoOne cgeo_one(const hmc_ctx* c, int npf) { return CGeoOne{c->lat, c->bc, npf}; }
 static CGeoBatch cgeo_batch(const hmc_ctx* c) { return CGeoBatch{c->bi.chains, c->bi.cblocks}; }
@@ -700,12 +741,13 @@ struct Launch {
     Geo cg, pxy, pt;
     int ncg = 0, npxy = 0, npt = 0;
     size_t lds_xy = 0, lds_t = 0;
+    int xy_threads = 0;   // slice-pass workgroup size
     int pt_threads = 0;   // tau-pass workgroup size (64 columns x chunks per column)
     bool pt_full = false; // every chunk of the tau pass is full (the instantiation without
                           // per-step predicates)
     bool nn2 = false;     // the operator hops by two sites (the instantiations with those terms)
     bool pc = false;
-    bool r7 = false;      // some lattice extent has a factor 7 (radix-7 FFT stages)
+    bool wide = false;    // some lattice extent has an FFT radix above kFftNarrow
     // CG step A as a march (one lattice, nearest-neighbour operator): plan, threads, LDS and
     // workgroups per unit (0: the tile kernels k_cg_a / k_cg_a2)
     MarchPlan cgm{};
@@ -731,17 +773,19 @@ static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
     l.cg = geo_one(c, bpr);
     l.ncg = bpr * n;
     l.pc = c->p.precond == HMC_PRECOND_FOURIER && c->pc_ok[pi];
-    const int nxy = 4 * c->Lt, nt = 4 * pc_groups(c->lat.LL, kPcCols);
-    l.pxy = GeoOne{c->lat, bpr, nxy, c->pstride};
-    l.pt = GeoOne{c->lat, bpr, nt, c->pstride};
+    const SliceCut sc = c->pc_ok[pi] ? slice_cut<R>(c->L, 4LL * c->Lt * n) : SliceCut{1, c->L};
+    const int nxy = (4 * c->Lt + sc.spw - 1) / sc.spw, nt = 4 * pc_groups(c->lat.LL, kPcCols);
+    l.pxy = GeoOne{c->lat, bpr, nxy, c->pstride, sc};
+    l.pt = GeoOne{c->lat, bpr, nt, c->pstride, SliceCut{}};
     l.npxy = nxy * n;
     l.npt = nt * n;
-    l.lds_xy = c->lds_xy[pi];
+    l.lds_xy = slice_lds<R>(sc, c->L);
+    l.xy_threads = slice_threads(sc, c->L);
     l.lds_t = c->lds_t[pi];
     l.pt_threads = kPcCols * c->pc_q[pi];
     l.pt_full = c->pc_full[pi];
     l.nn2 = c->cf64.nn2 != 0;
-    l.r7 = c->pc_r7;
+    l.wide = c->pc_wide;
     l.cgbm = c->cgb_march[pi] != 0;
     // step A as a march: rows per band so that the band and its two neighbour rows have one
     // thread each (at most kMarchCgThreads); slices per segment for about one workgroup per
@@ -788,16 +832,17 @@ static Launch<GeoBatch> launch_batch(const hmc_ctx* c) {
     l.cg = geo_batch(c, pi);
     l.ncg = c->bi.nblocks[pi];
     l.pc = c->p.precond == HMC_PRECOND_FOURIER && c->pc_ok[pi];
-    l.pxy = GeoBatch{c->bi.units[pi], c->bi.pxy_blocks};
+    l.pxy = GeoBatch{c->bi.units[pi], c->bi.pxy_blocks[pi]};
     l.pt = GeoBatch{c->bi.units[pi], c->bi.pt_blocks[pi]};
-    l.npxy = c->bi.nslices;
+    l.npxy = c->bi.nslices[pi];
     l.npt = c->bi.ngroups[pi];
     l.lds_xy = c->lds_xy[pi];
+    l.xy_threads = c->bi.xy_threads[pi];
     l.lds_t = c->lds_t[pi];
     l.pt_threads = kPcCols * c->pc_q[pi];
     l.pt_full = c->pc_full[pi];
     l.nn2 = c->cf64.nn2 != 0;
-    l.r7 = c->pc_r7;
+    l.wide = c->pc_wide;
     l.cgbm = c->cgb_march[pi] != 0;
     if (!l.nn2 && c->bi.mgrid[pi] > 0) {
         l.bm = MGeoBatch{c->bi.units[pi], c->bi.mblocks[pi], 0};
@@ -877,7 +922,7 @@ template <typename R, class Geo, int MAXR>
 static int enqueue_pc_r(hmc_ctx* c, const Launch<Geo>& lc, const CgVecs<R>& v, int expect1, hipStream_t s,
                         hipEvent_t* e) {
     // e: null, or the start/stop events of the three passes (timed by their own dispatches)
-    launch_timed(k_pc_xy<R, false, Geo, MAXR>, lc.npxy, kPcBlock, lc.lds_xy, s, e, 0,
+    launch_timed(k_pc_xy<R, false, Geo, MAXR>, lc.npxy, lc.xy_threads, lc.lds_xy, s, e, 0,
                  next_ctl(c, expect1), lc.pxy, v.r, v.z, c->blob);
     LAUNCHCHK();
     if (lc.pt_full)
@@ -887,7 +932,7 @@ static int enqueue_pc_r(hmc_ctx* c, const Launch<Geo>& lc, const CgVecs<R>& v, i
         launch_timed(k_pc_t<R, Geo, false>, lc.npt, lc.pt_threads, lc.lds_t, s, e, 1,
                      next_ctl(c, PEND_NONE), lc.pt, v.z, c->blob, c->cf64);
     LAUNCHCHK();
-    launch_timed(k_pc_xy<R, true, Geo, MAXR>, lc.npxy, kPcBlock, lc.lds_xy, s, e, 2,
+    launch_timed(k_pc_xy<R, true, Geo, MAXR>, lc.npxy, lc.xy_threads, lc.lds_xy, s, e, 2,
                  next_ctl(c, PEND_RZ), lc.pxy, v.z, v.z, c->blob);
     LAUNCHCHK();
     return HMC_OK;
@@ -896,7 +941,8 @@ static int enqueue_pc_r(hmc_ctx* c, const Launch<Geo>& lc, const CgVecs<R>& v, i
 template <typename R, class Geo>
 static int enqueue_pc(hmc_ctx* c, const Launch<Geo>& lc, const CgVecs<R>& v, int expect1, hipStream_t s,
                       hipEvent_t* e = nullptr) {
-    return lc.r7 ? enqueue_pc_r<R, Geo, 7>(c, lc, v, expect1, s, e) : enqueue_pc_r<R, Geo, 5>(c, lc, v, expect1, s, e);
+    return lc.wide ? enqueue_pc_r<R, Geo, kFftMaxRadix>(c, lc, v, expect1, s, e)
+                   : enqueue_pc_r<R, Geo, kFftNarrow>(c, lc, v, expect1, s, e);
 }
 
 // Launches of one status chunk (kept even, so that every chunk starts at the same record
@@ -1505,16 +1551,18 @@ static int read_slots(hmc_ctx* c, hipStream_t s) {
 // (the FP64 CG vector t, idle outside solves), the tau pass (the reduction `red`, scaled by
 // rs, into slots[slot]; the accumulation into acc; the scaling `mul`), and with `mul` the
 // inverse slice FFT into out (add: out += h y; else out = y).  in may equal out.
-template <int MAXR>
+template <int XY, int T>
 static int metric_passes_r(hmc_ctx* c, const double* in, double* out, int add, double h, int mul, int red,
                            double rs, double* acc, int slot, hipStream_t s, int acc_add) {
-    const MetricGeo g{c->lat.L, c->lat.Lt, c->lat.LL, c->lat.vol};
+    const MetricGeo g{c->lat.L, c->lat.Lt, c->lat.LL, c->lat.vol, c->mt_cut.pitch};
     double2* scr = c->t64;
     const int nslice = 3 * g.Lt, ngrp = 3 * pc_groups(g.LL, pc_ncol<double>());
-    hipLaunchKernelGGL((k_mt_xy<false, MAXR>), dim3(nslice), dim3(kPcBlock), c->lds_xy[0], s, g, in, scr,
+    const size_t mt_lds = slice_lds<double>(c->mt_cut, g.L);
+    const int mt_threads = slice_threads(c->mt_cut, g.L);
+    hipLaunchKernelGGL((k_mt_xy<false, XY>), dim3(nslice), dim3(mt_threads), mt_lds, s, g, in, scr,
                        static_cast<double*>(nullptr), 0, 0.0, c->blob);
     LAUNCHCHK();
-    hipLaunchKernelGGL((k_mt_t<MAXR>), dim3(ngrp), dim3(kPcBlock), c->lds_mt_t, s, g, scr, c->sigma, mul, red, rs,
+    hipLaunchKernelGGL((k_mt_t<T>), dim3(ngrp), dim3(kPcBlock), c->lds_mt_t, s, g, scr, c->sigma, mul, red, rs,
                        acc, acc_add, red ? c->mpart : static_cast<double*>(nullptr), c->blob);
     LAUNCHCHK();
     if (red) {
@@ -1522,7 +1570,7 @@ static int metric_passes_r(hmc_ctx* c, const double* in, double* out, int add, d
         LAUNCHCHK();
     }
     if (mul) {
-        hipLaunchKernelGGL((k_mt_xy<true, MAXR>), dim3(nslice), dim3(kPcBlock), c->lds_xy[0], s, g,
+        hipLaunchKernelGGL((k_mt_xy<true, XY>), dim3(nslice), dim3(mt_threads), mt_lds, s, g,
                            static_cast<const double*>(nullptr), scr, out, add, h, c->blob);
         LAUNCHCHK();
     }
@@ -1531,8 +1579,13 @@ static int metric_passes_r(hmc_ctx* c, const double* in, double* out, int add, d
 
 static int metric_passes(hmc_ctx* c, const double* in, double* out, int add, double h, int mul, int red,
                          double rs, double* acc, int slot, hipStream_t s, int acc_add = 1) {
-    return c->pc_r7 ? metric_passes_r<7>(c, in, out, add, h, mul, red, rs, acc, slot, s, acc_add)
-                    : metric_passes_r<5>(c, in, out, add, h, mul, red, rs, acc, slot, s, acc_add);
+    auto go = [&](auto xy, auto t) {
+        return metric_passes_r<decltype(xy)::value, decltype(t)::value>(c, in, out, add, h, mul, red, rs, acc, slot, s,
+                                                                        acc_add);
+    };
+    using N = std::integral_constant<int, kFftNarrow>;
+    using W = std::integral_constant<int, kFftMaxRadix>;
+    return c->pc_wide ? (c->mt_wide ? go(W{}, W{}) : go(W{}, N{})) : (c->mt_wide ? go(N{}, W{}) : go(N{}, N{}));
 }
 
 // The leapfrog drift phi += eps dphi/dt: eps pi (identity metric) or eps Sigma pi.
@@ -1629,25 +1682,36 @@ static void pc_setup(hmc_ctx* c) {
     else lats.push_back(c->lat);
     bool plans = true;
     long long blob = 0;
-    c->pc_r7 = false;
+    c->pc_wide = c->mt_wide = false;
     c->bi.pcoff.assign(1, 0);
-    c->bi.nslices = 0;
+    c->bi.nslices[0] = c->bi.nslices[1] = 0;
+    c->bi.xy_threads[0] = c->bi.xy_threads[1] = 64;
     c->bi.ngroups[0] = c->bi.ngroups[1] = 0;
+    size_t least[2] = {0, 0};
     for (int pi = 0; pi < 2; ++pi) c->lds_xy[pi] = c->lds_t[pi] = 0, c->pc_q[pi] = 0, c->pc_full[pi] = false;
     for (const Lat& l : lats) {
         FftPlan pa, pb;
         const bool ok = make_fft_plan(l.L, pa) && make_fft_plan(l.Lt, pb);
         plans = plans && ok;
-        if (ok) c->pc_r7 = c->pc_r7 || fft_max_radix(pa) == 7 || fft_max_radix(pb) == 7;
+        if (ok) {
+            c->pc_wide = c->pc_wide || fft_max_radix(pa) > kFftNarrow;
+            c->mt_wide = c->mt_wide || fft_max_radix(pb) > kFftNarrow;
+        }
         blob += pc_blob_layout(l.L, l.Lt).size;
         c->bi.pcoff.push_back(blob);
         const int nrhs = c->is_batch ? c->bi.nrhs : 1;
-        c->bi.nslices += 4 * l.Lt * nrhs;
         c->bi.ngroups[0] += 4 * pc_groups(l.LL, kPcCols) * nrhs;
         c->bi.ngroups[1] += 4 * pc_groups(l.LL, kPcCols) * nrhs;
         const size_t c64 = sizeof(double2), c32 = sizeof(float2);
-        c->lds_xy[0] = std::max(c->lds_xy[0], size_t(l.LL + l.L) * c64);
-        c->lds_xy[1] = std::max(c->lds_xy[1], size_t(l.LL + l.L) * c32);
+        // the least a slice needs (pitch L) decides what is supported
+        least[0] = std::max(least[0], size_t(l.LL + l.L) * c64);
+        least[1] = std::max(least[1], size_t(l.LL + l.L) * c32);
+        for (int pi = 0; ok && pi < 2; ++pi) {
+            const SliceCut sc = pi ? slice_cut<float>(l.L, 1LL << 40) : slice_cut<double>(l.L, 1LL << 40);
+            c->bi.nslices[pi] += (4 * l.Lt + sc.spw - 1) / sc.spw * nrhs;
+            c->lds_xy[pi] = std::max(c->lds_xy[pi], pi ? slice_lds<float>(sc, l.L) : slice_lds<double>(sc, l.L));
+            c->bi.xy_threads[pi] = std::max(c->bi.xy_threads[pi], slice_threads(sc, l.L));
+        }
         const int q64 = pc_chunks<double>(l.Lt), q32 = pc_chunks<float>(l.Lt);
         c->pc_q[0] = (q64 == 0 || c->pc_q[0] < 0) ? -1 : std::max(c->pc_q[0], q64);
         c->pc_q[1] = (q32 == 0 || c->pc_q[1] < 0) ? -1 : std::max(c->pc_q[1], q32);
@@ -1662,12 +1726,13 @@ static void pc_setup(hmc_ctx* c) {
     c->lds_t[0] = c->pc_q[0] > 0 ? pc_tau_lds<double>(c->pc_q[0]) : 0;
     c->lds_t[1] = c->pc_q[1] > 0 ? pc_tau_lds<float>(c->pc_q[1]) : 0;
     for (int pi = 0; pi < 2; ++pi)
-        c->pc_ok[pi] = plans && c->pc_q[pi] > 0 && c->lds_xy[pi] <= size_t(maxlds) &&
+        c->pc_ok[pi] = plans && c->pc_q[pi] > 0 && least[pi] <= size_t(maxlds) &&
                        c->lds_t[pi] <= size_t(maxlds);
     if (!c->is_batch) {
         const Lat& l = c->lat;
         c->lds_mt_t = size_t(l.Lt) * (pc_ncol<double>() + 1) * sizeof(double2) + size_t(l.Lt + l.L) * sizeof(int);
-        c->metric_ok = plans && c->lds_xy[0] <= size_t(maxlds) && c->lds_mt_t <= size_t(maxlds);
+        c->metric_ok = plans && least[0] <= size_t(maxlds) && c->lds_mt_t <= size_t(maxlds);
+        c->mt_cut = SliceCut{1, slice_pitch<double>(c->L, 1)};
     }
 }
 
@@ -1681,7 +1746,8 @@ static int check_precond(const hmc_ctx* c, const hmc_params* p) {
 
 // Allow the preconditioner passes their dynamic LDS (above the default per-workgroup amount).
 template <typename R, class Geo, int MAXR>
-static void pc_lds_attributes_r(size_t xy, size_t t) {
+static void pc_lds_attributes_r(size_t t) {
+    const size_t xy = kPcLdsMost;
     const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_xy<R, false, Geo, MAXR>), a, int(xy));
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_xy<R, true, Geo, MAXR>), a, int(xy));
@@ -1692,12 +1758,12 @@ static void pc_lds_attributes_r(size_t xy, size_t t) {
 template <class Geo>
 static void pc_lds_attributes(const hmc_ctx* c) {
     if (c->pc_ok[0]) {
-        if (c->pc_r7) pc_lds_attributes_r<double, Geo, 7>(c->lds_xy[0], c->lds_t[0]);
-        else pc_lds_attributes_r<double, Geo, 5>(c->lds_xy[0], c->lds_t[0]);
+        if (c->pc_wide) pc_lds_attributes_r<double, Geo, kFftMaxRadix>(c->lds_t[0]);
+        else pc_lds_attributes_r<double, Geo, kFftNarrow>(c->lds_t[0]);
     }
     if (c->pc_ok[1]) {
-        if (c->pc_r7) pc_lds_attributes_r<float, Geo, 7>(c->lds_xy[1], c->lds_t[1]);
-        else pc_lds_attributes_r<float, Geo, 5>(c->lds_xy[1], c->lds_t[1]);
+        if (c->pc_wide) pc_lds_attributes_r<float, Geo, kFftMaxRadix>(c->lds_t[1]);
+        else pc_lds_attributes_r<float, Geo, kFftNarrow>(c->lds_t[1]);
     }
     (void)hipGetLastError();
 }
@@ -1717,17 +1783,21 @@ static int upload_pc(hmc_ctx* c) {
     if (!all.empty()) HIPCHK(hipMemcpy(c->blob, all.data(), sizeof(double) * all.size(), hipMemcpyHostToDevice));
     if (c->is_batch) {
         BatchInfo& b = c->bi;
-        std::vector<int2> xy, t[2];
+        std::vector<int2> xy[2], t[2];
         for (int ch = 0; ch < b.nchains; ++ch) {
             const Lat& l = b.lats[size_t(ch)];
             for (int k = 0; k < b.nrhs; ++k) {
                 const int u = ch * b.nrhs + k;
-                for (int r = 0; r < 4 * l.Lt; ++r) xy.push_back(make_int2(u, r));
+                for (int pi = 0; pi < 2; ++pi) {
+                    const int spw = b.hunits[pi][size_t(u)].sc.spw;
+                    for (int r = 0; r < (4 * l.Lt + spw - 1) / spw; ++r) xy[pi].push_back(make_int2(u, r));
+                }
                 for (int r = 0; r < 4 * pc_groups(l.LL, kPcCols); ++r) t[0].push_back(make_int2(u, r));
                 for (int r = 0; r < 4 * pc_groups(l.LL, kPcCols); ++r) t[1].push_back(make_int2(u, r));
             }
         }
-        HIPCHK(hipMemcpy(b.pxy_blocks, xy.data(), sizeof(int2) * xy.size(), hipMemcpyHostToDevice));
+        for (int pi = 0; pi < 2; ++pi)
+            HIPCHK(hipMemcpy(b.pxy_blocks[pi], xy[pi].data(), sizeof(int2) * xy[pi].size(), hipMemcpyHostToDevice));
         for (int pi = 0; pi < 2; ++pi)
             HIPCHK(hipMemcpy(b.pt_blocks[pi], t[pi].data(), sizeof(int2) * t[pi].size(), hipMemcpyHostToDevice));
         pc_lds_attributes<GeoBatch>(c);
@@ -1735,12 +1805,12 @@ static int upload_pc(hmc_ctx* c) {
         pc_lds_attributes<GeoOne>(c);
         if (c->metric_ok) {
             const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, 5>), a, int(c->lds_xy[0]));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, 5>), a, int(c->lds_xy[0]));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_t<5>), a, int(c->lds_mt_t));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, 7>), a, int(c->lds_xy[0]));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, 7>), a, int(c->lds_xy[0]));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_t<7>), a, int(c->lds_mt_t));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, kFftNarrow>), a, int(kPcLdsMost));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, kFftNarrow>), a, int(kPcLdsMost));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_t<kFftNarrow>), a, int(c->lds_mt_t));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, kFftMaxRadix>), a, int(kPcLdsMost));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, kFftMaxRadix>), a, int(kPcLdsMost));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_t<kFftMaxRadix>), a, int(c->lds_mt_t));
             (void)hipGetLastError();
         }
     }
@@ -2243,8 +2313,10 @@ int hmc_test_fft(int n, int inverse, const double* in, double* out) {
         buf[size_t(i)] = make_double2(in[2 * i], in[2 * i + 1]);
         tw[size_t(i)] = twiddle_host(i, n);
     }
-    if (inverse) fft_lines<double, true>(ExHost(), buf.data(), 1, n, 1, pl, tw.data());
-    else fft_lines<double, false>(ExHost(), buf.data(), 1, n, 1, pl, tw.data());
+    Lines ln{1, 1, n, n, 1, {}};
+    ln.dcnt.init(1);
+    if (inverse) fft_lines<double, true>(ExHost(), buf.data(), ln, pl, tw.data(), 0, pl.nst);
+    else fft_lines<double, false>(ExHost(), buf.data(), ln, pl, tw.data(), 0, pl.nst);
     for (int i = 0; i < n; ++i) {
         out[2 * i] = buf[size_t(i)].x;
         out[2 * i + 1] = buf[size_t(i)].y;
@@ -2274,17 +2346,25 @@ int hmc_test_precond(int L, int Lt, double dtau, const hmc_params* params, const
     const PcBlob bl = pc_blob_layout(L, Lt);
     const double2* twl = reinterpret_cast<const double2*>(blob.data() + bl.twl);
     const ExHost ex;
-    std::vector<double2> sbuf(static_cast<size_t>(LL));   // the kernels' LDS copy of a slice
-    for (int sl = 0; sl < 4 * Lt; ++sl) {
-        double2* slice = w.data() + size_t(sl) * LL;
-        fft_slice_io<double, false>(ex, slice, sbuf.data(), slice, pl, twl);
-    }
+    // the slice passes in groups of two slices (their last one may have one), as the kernels' LDS
+    // copies hold them
+    const int P = L + 1;
+    std::vector<double2> sbuf(size_t(2) * L * P);
+    auto slices = [&](auto inv) {
+        for (int sl = 0; sl < 4 * Lt; sl += 2) {
+            double2* slice = w.data() + size_t(sl) * LL;
+            fft_slices<double, decltype(inv)::value>(
+                ex, [&](int i) { return slice[i]; }, sbuf.data(), [&](int i, double2 v) { slice[i] = v; },
+                std::min(2, 4 * Lt - sl), P, pl, twl);
+        }
+    };
+    slices(std::false_type{});
     // the tau pass as the kernel runs it: Q chunks per column, each reduced to an affine map,
     // the maps closed around the cycle, the chunks rerun from their entering values
     double acc = 0.0;
     for (int c = 0; c < 4; ++c) {
         for (int col = 0; col < LL; ++col) {
-            const double b = pc_column_b(col, L, c >> 1, blob.data() + bl.cosx, cf);
+            const double b = pc_column_b(col, pl, c >> 1, blob.data() + bl.cosx, cf);
             const RecCoef<double> k = rec_coef(b);
             constexpr int QM = pc_max_chunks<double>();
             double2 ch[QM][MC], sc[QM], sx[QM + 1];
@@ -2322,10 +2402,7 @@ int hmc_test_precond(int L, int Lt, double dtau, const hmc_params* params, const
             }
         }
     }
-    for (int sl = 0; sl < 4 * Lt; ++sl) {
-        double2* slice = w.data() + size_t(sl) * LL;
-        fft_slice_io<double, true>(ex, slice, sbuf.data(), slice, pl, twl);
-    }
+    slices(std::true_type{});
     for (size_t i = 0; i < w.size(); ++i) {
         out[2 * i] = w[i].x;
         out[2 * i + 1] = w[i].y;

@@ -133,6 +133,12 @@ __host__ __device__ inline MarchPlan make_march_plan(int L, int Lt, int R, int s
     return p;
 }
 
+// Work of one workgroup of the preconditioner's slice passes: consecutive (component, tau) slices
+// and the row pitch of their working copies in LDS.
+struct SliceCut {
+    int spw, pitch;
+};
+
 // One right-hand side of one lattice: the unit the CG state machine tracks.  A solve on a
 // single lattice has one unit per right-hand side; a batch of independent lattices (chains)
 // of different sizes has one per (chain, right-hand side), all in one launch.
@@ -148,6 +154,7 @@ struct UnitDesc {
     int mparts;         // its workgroups (bands x segments); 0: the tile kernels
     MarchPlan rmp;      // the reliable update's FP64 marches
     int rparts;         // their workgroups; 0: the tile kernels
+    SliceCut sc;        // slices per workgroup of the preconditioner's slice passes
 };
 
 // Where a workgroup works: its unit and its rank within the unit.
@@ -161,6 +168,7 @@ struct UPos {
     int pcoff;          // first double of the preconditioner tables of its lattice
     int mparts;         // batch: workgroups of the unit's step-A march (0 for one lattice)
     int rparts;         // batch: workgroups of the unit's reliable-update marches
+    SliceCut sc;
 };
 
 // One lattice: unit k = right-hand side k; a launch runs nblk workgroups per unit in k-major
@@ -171,6 +179,7 @@ struct GeoOne {
     int bpr;
     int nblk;
     int pstride;
+    SliceCut sc;
     __device__ __forceinline__ UPos unit(int k, int blk) const {
         UPos p;
         p.lat = lat;
@@ -182,6 +191,7 @@ struct GeoOne {
         p.part = k * pstride;
         p.pcoff = 0;
         p.mparts = p.rparts = 0;
+        p.sc = sc;
         return p;
     }
     __device__ __forceinline__ UPos at(int logical) const {
@@ -207,6 +217,7 @@ struct GeoBatch {
         p.pcoff = u.pcoff;
         p.mparts = u.mparts;
         p.rparts = u.rparts;
+        p.sc = u.sc;
         return p;
     }
     __device__ __forceinline__ UPos at(int logical) const {
@@ -1191,6 +1202,7 @@ __global__ __launch_bounds__(kBlock) void k_dot_re(CGeo geo, const double2* __re
     if (threadIdx.x == 0) part[logical] = v[0];
 }
 
+#ifndef HMC_FFT_SOURCE   // kernels without template parameters belong to one source
 // One workgroup per lattice c: out[c * out_stride + q] = sum of part[q * stride + j] over the
 // lattice's workgroups j in [first[c], first[c + 1]), q < nq, in index order.
 __global__ __launch_bounds__(kBlock) void k_sum_chains(const double* __restrict__ part, int stride,
@@ -1227,5 +1239,6 @@ __global__ __launch_bounds__(kBlock) void k_to_f32(const double* __restrict__ a,
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i < n) b[i] = float(a[i]);
 }
+#endif
 
 }  // namespace hmc

@@ -316,6 +316,7 @@ __device__ __forceinline__ UPos march_unit(const Lat& lat, int k, int blk, int n
     p.part = k * pstride;
     p.pcoff = 0;
     p.mparts = p.rparts = 0;
+    p.sc = SliceCut{};
     return p;
 }
 

@@ -16,11 +16,60 @@
 
 namespace hmc {
 
+// Stage n complex elements between global memory and LDS: element i of the set lives at g(i)
+// in global memory and at lds[i].  Up to 64 bytes of loads are in flight per thread before
+// their LDS writes (a plain loop would wait out the memory latency once per element).  The
+// components are kept in separate arrays so that they stay in registers.
+template <typename R, class G>
+__device__ __forceinline__ void stage_in(C2<R>* __restrict__ lds, int n, G g) {
+    constexpr int U = sizeof(R) == 4 ? 8 : 4;
+    const int nt = blockDim.x;
+    for (int i0 = threadIdx.x; i0 < n; i0 += nt * U) {
+        R vx[U], vy[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * nt;
+            if (i < n) {
+                const C2<R> v = *g(i);
+                vx[u] = v.x;
+                vy[u] = v.y;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * nt;
+            if (i < n) lds[i] = mk<R>(vx[u], vy[u]);
+        }
+    }
+}
+template <typename R, class G>
+__device__ __forceinline__ void stage_out(const C2<R>* __restrict__ lds, int n, G g) {
+    constexpr int U = sizeof(R) == 4 ? 8 : 4;
+    const int nt = blockDim.x;
+    for (int i0 = threadIdx.x; i0 < n; i0 += nt * U) {
+        R vx[U], vy[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * nt;
+            if (i < n) {
+                const C2<R> v = lds[i];
+                vx[u] = v.x;
+                vy[u] = v.y;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * nt;
+            if (i < n) *g(i) = mk<R>(vx[u], vy[u]);
+        }
+    }
+}
+
 enum MetricMul : int { MUL_SIGMA = 1, MUL_RSQRT = 2 };
 enum MetricRed : int { RED_NONE = 0, RED_SIGMA = 1, RED_INV = 2, RED_PLAIN = 3 };
 
 struct MetricGeo {
-    int L, Lt, LL, vol;
+    int L, Lt, LL, vol, pitch;
 };
 
 // One workgroup per (component, slice).  Forward: scr = FFT2(in, 0).  Inverse: the inverse
@@ -33,25 +82,24 @@ __global__ __launch_bounds__(kPcBlock) void k_mt_xy(MetricGeo g, const double* _
     const int b = xcd_remap(blockIdx.x, gridDim.x);
     const int L = g.L, LL = g.LL;
     double2* buf = reinterpret_cast<double2*>(pc_smem);
-    double2* tw = buf + LL;
+    double2* tw = buf + L * g.pitch;
     const PcBlob bl = pc_blob_layout(L, g.Lt);
-    for (int i = threadIdx.x; i < L; i += kPcBlock) tw[i] = make_double2(blob[bl.twl + 2 * i], blob[bl.twl + 2 * i + 1]);
-    __shared__ FftPlan pl;
-    if (threadIdx.x == 0) make_fft_plan(L, pl);
+    for (int i = threadIdx.x; i < L; i += blockDim.x) tw[i] = make_double2(blob[bl.twl + 2 * i], blob[bl.twl + 2 * i + 1]);
+    const FftPlan& pl = blob_plan(blob, bl.planL);
     const size_t o = size_t(b) * LL;   // slice tau of component l: b = l N_tau + tau
-    if (!INV) {
-        for (int i = threadIdx.x; i < LL; i += kPcBlock) buf[i] = make_double2(in[o + i], 0.0);
-    } else {
-        stage_in<double>(buf, LL, [&](int i) { return scr + o + i; });
-    }
     __syncthreads();
-    fft_slice<double, INV, MAXR>(ExDevice(), buf, pl, tw);
-    if (!INV) {
-        stage_out<double>(buf, LL, [&](int i) { return scr + o + i; });
-    } else if (add) {
-        for (int i = threadIdx.x; i < LL; i += kPcBlock) out[o + i] = out[o + i] + h * buf[i].x;
+    if constexpr (!INV) {
+        const double* v = in + o;
+        double2* w = scr + o;
+        fft_slices<double, false, MAXR>(
+            ExDevice(), [&](int i) HMC_FLAT { return make_double2(v[i], 0.0); }, buf, [&](int i, double2 y) HMC_FLAT { w[i] = y; }, 1,
+            g.pitch, pl, tw);
     } else {
-        for (int i = threadIdx.x; i < LL; i += kPcBlock) out[o + i] = buf[i].x;
+        const double2* w = scr + o;
+        double* y = out + o;
+        fft_slices<double, true, MAXR>(
+            ExDevice(), [&](int i) HMC_FLAT { return w[i]; }, buf,
+            [&](int i, double2 v) HMC_FLAT { y[i] = add ? y[i] + h * v.x : v.x; }, 1, g.pitch, pl, tw);
     }
 }
 
@@ -78,15 +126,12 @@ __global__ __launch_bounds__(kPcBlock) void k_mt_t(MetricGeo g, double2* __restr
     int* fL = fT + Lt;
     const PcBlob bl = pc_blob_layout(L, Lt);
     for (int i = threadIdx.x; i < Lt; i += kPcBlock) twT[i] = make_double2(blob[bl.twT + 2 * i], blob[bl.twT + 2 * i + 1]);
-    __shared__ FftPlan pt, pl;
-    if (threadIdx.x == 0) make_fft_plan(Lt, pt);
-    if (threadIdx.x == 1) make_fft_plan(L, pl);
-    __syncthreads();
+    const FftPlan &pt = blob_plan(blob, bl.planT), &pl = blob_plan(blob, bl.planL);
     for (int i = threadIdx.x; i < Lt; i += kPcBlock) fT[i] = fft_freq(pt, i);
     for (int i = threadIdx.x; i < L; i += kPcBlock) fL[i] = fft_freq(pl, i);
-    FastDiv dc, dL;
+    Div32 dc;
     dc.init(uint32_t(ncol));
-    dL.init(uint32_t(L));
+    const Lines lines{ncol, ncol, 1, 0, 1, dc};
     const size_t o = size_t(l) * g.vol + size_t(col0);
     auto at = [&](int i) {
         const int tau = int(dc.div(uint32_t(i)));
@@ -94,15 +139,15 @@ __global__ __launch_bounds__(kPcBlock) void k_mt_t(MetricGeo g, double2* __restr
     };
     stage_in<double>(buf, Lt * ncol, at);
     __syncthreads();
-    fft_lines<double, false, MAXR>(ExDevice(), buf, ncol, 1, ncol, pt, twT);
+    fft_lines<double, false, MAXR>(ExDevice(), buf, lines, pt, twT, 0, pt.nst);
     const double inv_v = 1.0 / double(g.vol);
     const double* sg = sigma ? sigma + size_t(l) * g.vol : nullptr;
     double* ac = acc ? acc + size_t(l) * g.vol : nullptr;
     double sum[1] = {0.0};
     for (int i = threadIdx.x; i < Lt * ncol; i += kPcBlock) {
         const int p = int(dc.div(uint32_t(i))), j = i - p * ncol;
-        const int col = col0 + j;
-        const int px = int(dL.div(uint32_t(col))), py = col - px * L;
+        int px, py;
+        fft_slice_pos(pl, col0 + j, px, py);
         const size_t k = (size_t(fT[p]) * L + fL[px]) * L + fL[py];
         const double sv = sg ? sg[k] : 1.0;
         const double2 y = buf[i];
@@ -119,11 +164,12 @@ __global__ __launch_bounds__(kPcBlock) void k_mt_t(MetricGeo g, double2* __restr
     block_reduce<1>(sum);   // ends with a barrier
     if (part != nullptr && threadIdx.x == 0) part[b] = rs * sum[0];
     if (mul) {
-        fft_lines<double, true, MAXR>(ExDevice(), buf, ncol, 1, ncol, pt, twT);
+        fft_lines<double, true, MAXR>(ExDevice(), buf, lines, pt, twT, 0, pt.nst);
         stage_out<double>(buf, Lt * ncol, at);
     }
 }
 
+#ifndef HMC_FFT_SOURCE
 // chi(k) += scale ((t0(k) + t1(k)) + t2(k)) for the three component planes of t (each vol
 // long): one term of the SDW susceptibility of Eq. (34) from the per-component spectra.
 __global__ __launch_bounds__(kBlock) void k_mt_sum3(const double* __restrict__ t, double* __restrict__ chi,
@@ -142,5 +188,6 @@ __global__ __launch_bounds__(kBlock) void k_mt_csum(const double* __restrict__ p
     block_reduce<1>(v);
     if (threadIdx.x == 0) part[size_t(l) * nb + b] = v[0];
 }
+#endif
 
 }  // namespace hmc

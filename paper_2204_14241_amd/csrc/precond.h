@@ -25,9 +25,10 @@ __host__ __device__ constexpr int pc_ncol() { return int(256 / sizeof(C2<R>)); }
 
 __host__ __device__ __forceinline__ int pc_groups(int LL, int ncol) { return (LL + ncol - 1) / ncol; }
 
-// Workgroup size of the slice passes: a slice is one workgroup's LDS, and only a few fit a
-// CU, so each gets more threads (more loads in flight, shorter FFT phase).
+// Largest workgroup of the slice passes, and the LDS one may take (with the kernel's own use, the
+// 160 KB of a CU).
 constexpr int kPcBlock = 512;
+constexpr size_t kPcLdsMost = (size_t(160) << 10) - 2048;
 
 constexpr int kPcCols = 64;     // columns per tau-pass workgroup
 
@@ -49,55 +50,8 @@ __host__ __device__ inline int pc_chunks(int Lt) {
     return q > pc_max_chunks<R>() ? 0 : (q < 1 ? 1 : q);
 }
 
-// Stage n complex elements between global memory and LDS: element i of the set lives at g(i)
-// in global memory and at lds[i].  Up to 64 bytes of loads are in flight per thread before
-// their LDS writes (a plain loop would wait out the memory latency once per element).  The
-// components are kept in separate arrays so that they stay in registers.
-template <typename R, class G>
-__device__ __forceinline__ void stage_in(C2<R>* __restrict__ lds, int n, G g) {
-    constexpr int U = sizeof(R) == 4 ? 8 : 4;
-    const int nt = blockDim.x;
-    for (int i0 = threadIdx.x; i0 < n; i0 += nt * U) {
-        R vx[U], vy[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * nt;
-            if (i < n) {
-                const C2<R> v = *g(i);
-                vx[u] = v.x;
-                vy[u] = v.y;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * nt;
-            if (i < n) lds[i] = mk<R>(vx[u], vy[u]);
-        }
-    }
-}
-template <typename R, class G>
-__device__ __forceinline__ void stage_out(const C2<R>* __restrict__ lds, int n, G g) {
-    constexpr int U = sizeof(R) == 4 ? 8 : 4;
-    const int nt = blockDim.x;
-    for (int i0 = threadIdx.x; i0 < n; i0 += nt * U) {
-        R vx[U], vy[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * nt;
-            if (i < n) {
-                const C2<R> v = lds[i];
-                vx[u] = v.x;
-                vy[u] = v.y;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * nt;
-            if (i < n) *g(i) = mk<R>(vx[u], vy[u]);
-        }
-    }
-}
-
+// One workgroup: pos.sc.spw consecutive (component, tau) slices of a unit, from its slice
+// blk * spw on (they lie one after another in memory).  What bounds it: see fft.h.
 template <typename R, bool INV, class Geo, int MAXR>
 __global__ __launch_bounds__(kPcBlock) void k_pc_xy(CgCtl ctl, Geo geo, const C2<R>* src, C2<R>* dst,
                                                   const double* __restrict__ blob) {
@@ -106,7 +60,13 @@ __global__ __launch_bounds__(kPcBlock) void k_pc_xy(CgCtl ctl, Geo geo, const C2
     const Lat& lat = pos.lat;
     const int L = lat.L, LL = lat.LL;
     const int nparts = INV ? 4 * pc_groups(LL, kPcCols) : pos.bpr;
-    const int got = cg_finalize(ctl, pos, nparts);
+    const int s0 = pos.blk * pos.sc.spw, left = 4 * lat.Lt - s0, ns = left < pos.sc.spw ? left : pos.sc.spw;
+    C2<R>* buf = reinterpret_cast<C2<R>*>(pc_smem);
+    C2<R>* tw = buf + pos.sc.spw * L * pos.sc.pitch;
+    const PcBlob bl = pc_blob_layout(L, lat.Lt);
+    const double* B = blob + pos.pcoff;
+    for (int i = threadIdx.x; i < L; i += blockDim.x) tw[i] = mk<R>(R(B[bl.twl + 2 * i]), R(B[bl.twl + 2 * i + 1]));
+    const int got = cg_finalize(ctl, pos, nparts);   // ends with a barrier
     CgState& S = cg_shared();
     const bool work = S.pc && S.mode == CG_ACTIVE &&
                       (INV ? got == PEND_RZ : (got == PEND_RR || got == PEND_RU || got == PEND_BB));
@@ -115,18 +75,12 @@ __global__ __launch_bounds__(kPcBlock) void k_pc_xy(CgCtl ctl, Geo geo, const C2
         return;
     }
     if (!INV && threadIdx.x == 0) S.zstage = 1;
-    C2<R>* buf = reinterpret_cast<C2<R>*>(pc_smem);
-    C2<R>* tw = buf + LL;
-    const PcBlob bl = pc_blob_layout(L, lat.Lt);
-    const double* B = blob + pos.pcoff;
-    for (int i = threadIdx.x; i < L; i += kPcBlock) tw[i] = mk<R>(R(B[bl.twl + 2 * i]), R(B[bl.twl + 2 * i + 1]));
-    const int c = pos.blk / lat.Lt, tau = pos.blk - c * lat.Lt;
-    const size_t o = pos.voff + size_t(c) * lat.vol + size_t(tau) * LL;
-    __shared__ FftPlan pl;
-    if (threadIdx.x == 0) make_fft_plan(L, pl);
-    __syncthreads();
-    // the first stage reads the slice from src, the last writes it to dst
-    fft_slice_io<R, INV, MAXR>(ExDevice(), src + o, buf, dst + o, pl, tw);
+    const size_t o = pos.voff + size_t(s0) * LL;
+    const C2<R>* in = src + o;
+    C2<R>* out = dst + o;
+    fft_slices<R, INV, MAXR>(
+        ExDevice(), [&](int i) HMC_FLAT { return in[i]; }, buf, [&](int i, C2<R> v) HMC_FLAT { out[i] = v; }, ns, pos.sc.pitch,
+        blob_plan(B, bl.planL), tw);
     cg_publish(ctl, pos);
 }
 
@@ -276,10 +230,12 @@ __host__ __device__ inline void chunk_close(const R* a, const C2<R>* c, C2<R>* x
     }
 }
 
-// b of the column at slice position col (positions hold frequencies in digit-reversed order,
-// cosx is indexed by position).
-__host__ __device__ inline double pc_column_b(int col, int L, int band, const double* cosx, const Coef<double>& cf) {
-    const int px = col / L, py = col - px * L;
+// b of the column at index col of a transformed slice (fft_slice_pos; positions hold frequencies
+// in digit-reversed order, cosx is indexed by position).
+__host__ __device__ inline double pc_column_b(int col, const FftPlan& pl, int band, const double* cosx,
+                                              const Coef<double>& cf) {
+    int px, py;
+    fft_slice_pos(pl, col, px, py);
     const double cx = cosx[px], cy = cosx[py];
     return -cf.diag[band] - 2.0 * (cf.hop[band][0] * cx + cf.hop[band][1] * cy) -
            2.0 * (cf.hop2[band][0] * (2.0 * cx * cx - 1.0) + cf.hop2[band][1] * (2.0 * cy * cy - 1.0));
@@ -354,11 +310,14 @@ __host__ __device__ inline size_t pc_tau_lds(int Q) {
     return size_t(Q) * kPcCols * (sizeof(R) + sizeof(C2<R>)) + size_t(Q + 1) * kPcCols * sizeof(C2<R>);
 }
 
-// Pass 2: one workgroup per (component, group of 64 columns) of a unit, 64 Q threads (lane:
+// Pass 2 (FP32: six waves per SIMD asked for, 80 registers, so that two 640-thread workgroups share
+// a CU: 20.4 us at 80 x 80 x 200 against 26.8 us with the 86 the compiler takes by itself): one
+// workgroup per (component, group of 64 columns) of a unit, 64 Q threads (lane:
 // column, wavefront: chunk), Q = blockDim / 64 at least each lattice's pc_chunks.  FULL: every
 // lattice of the launch has N_tau = Q pc_chunk_max, so every chunk is full.
 template <typename R, class Geo, bool FULL>
-__global__ __launch_bounds__(kPcCols * pc_max_chunks<R>()) void k_pc_t(CgCtl ctl, Geo geo, C2<R>* z,
+__global__ __launch_bounds__(kPcCols * pc_max_chunks<R>()) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 6 : 1)))
+void k_pc_t(CgCtl ctl, Geo geo, C2<R>* z,
                                                             const double* __restrict__ blob, Coef<double> cf) {
     extern __shared__ __align__(16) unsigned char pc_smem[];
     constexpr int MC = pc_chunk_max<R>();
@@ -386,7 +345,8 @@ __global__ __launch_bounds__(kPcCols * pc_max_chunks<R>()) void k_pc_t(CgCtl ctl
     using N = typename std::conditional<FULL, FixedLen<MC>, int>::type;
     const N n = N(sp.n);
     const PcBlob bl = pc_blob_layout(L, Lt);
-    const R b = on ? R(pc_column_b(col, L, comp >> 1, blob + pos.pcoff + bl.cosx, cf)) : R(1);
+    const R b = on ? R(pc_column_b(col, blob_plan(blob + pos.pcoff, bl.planL), comp >> 1, blob + pos.pcoff + bl.cosx, cf))
+                   : R(1);
     const bool rev = !(b <= R(1) && b >= R(-1));   // K^{-1} runs backward: chunk held reversed
     // Element j of the chunk at byte offset o0 + j * ob from the chunk's first row (a base shared
     // by the wavefront), in 32 bits: at most pc_chunk_max rows of an L x L slice.
