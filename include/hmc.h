@@ -393,7 +393,9 @@ int hmc_get_mdm_shape(const hmc_ctx* ctx, int precision, int n, int* rows, int* 
  * consecutive slices in LDS and loading the next slice while it computes the current one, so
  * that every value of r (z), p, x and phi leaves HBM once.  rows = 0 switches back to the tile
  * kernels; slices = 0 picks about one workgroup per compute unit.  Default for one-lattice
- * contexts: 8 rows (FP32) / 4 rows (FP64), 8 slices, or the autotuner's choice.  precision:
+ * contexts: a cut estimated per launch from the lattice and the right-hand sides (8 rows FP32 / 4
+ * rows FP64 and 8 slices where the lattice fills the chip, fewer slices or other bands on smaller
+ * ones), or the autotuner's choice.  precision:
  * HMC_FP64, HMC_MIXED or -1 for both.  The algebra is that of the tile kernels; only the order
  * of the FP64 partial sums differs.  One-lattice contexts only (HMC_ERR_INVALID_ARG on a
  * batch: hmc_batch_set_cg_march); lattices whose band does not fit (rows + 2 rows, or rows + 4
@@ -401,7 +403,8 @@ int hmc_get_mdm_shape(const hmc_ctx* ctx, int precision, int n, int* rows, int* 
  * threads) keep the tile kernels.  The FP64 setting also cuts the reliable update's FP64
  * stencils into marches (nearest-neighbour operator). */
 int hmc_set_cg_march(hmc_ctx* ctx, int precision, int rows, int slices);
-/* The setting in use for `precision` (host ints; rows 0: the tile kernels). */
+/* The cut in use for `precision` (host ints; rows 0: the tile kernels); the default one is that of
+ * max_rhs right-hand sides. */
 int hmc_get_cg_march(const hmc_ctx* ctx, int precision, int* rows, int* slices);
 
 /* Whether CG step B (r -= alpha M^dagger t, Methods C) also marches when step A does, with
@@ -441,7 +444,7 @@ typedef struct hmc_tune_result {
  * caller's phi and right-hand sides b (n complex128 spinors, n <= max_rhs) with HIP events on
  * the stream: first at each candidate workgroup count of the tile kernels (12 multiples of 8
  * from 128 to 4096, capped at the tile count), then, for a one-lattice nearest-neighbour
- * context, at each step-A march shape (rows per band x slices per segment, up to 16 that fit)
+ * context, at each step-A march shape (the default cut, then rows per band x slices per segment, up to 16 that fit)
  * with the chosen count; keeps the fastest.  The choice is remembered process-wide for later
  * contexts of the same lattice, right-hand-side count and device, and written to an on-disk
  * cache keyed by (L, L_tau, right-hand sides, device, kernel-source hash): the file named by
@@ -523,8 +526,8 @@ int hmc_batch_set_step_graphs(hmc_batch* batch, int enable);
  * per thread in FP64, two in FP32), `slices` slices per segment (0: 8; more when a lattice's
  * partial-sum slots require it).  The reliable update uses the FP64 setting.  rows = 0 selects
  * the tile kernels; so does a lattice that fits no cut (then for the whole batch) and the
- * production model's two-site hops.  Defaults: 4 rows FP64, 8 FP32, 8 slices; hmc_batch_autotune
- * searches them.  precision: HMC_FP64, HMC_MIXED or -1 for both.  Results depend on the cut only
+ * production model's two-site hops.  Defaults: 4 rows FP64, 8 FP32, 8 slices (fewer where the
+ * batch would otherwise leave CUs without a workgroup); hmc_batch_autotune searches them.  precision: HMC_FP64, HMC_MIXED or -1 for both.  Results depend on the cut only
  * through the order of the FP64 partial sums; a chain reproduces, bit for bit, a one-lattice
  * context given the same cut.  hmc_batch_get_cg_march reports the cut chain `chain` uses in
  * `precision` (0 rows: the tile kernels) and whether step B marches with it. */

@@ -103,6 +103,11 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 static std::mutex g_scratch_mu;
 static std::map<int, void*> g_scratch_addr;   // device -> device address of `scratch`
 
+// A march cut: rows per band and slices per segment.
+struct Cut {
+    int rows = 0, slices = 0;
+};
+
 // Batch-mode description: nchains independent lattices, nrhs right-hand sides each.
 struct BatchInfo {
     int nchains = 0, nrhs = 0;
@@ -228,6 +233,10 @@ struct hmc_ctx {
     // per segment (0: the default)
     int cgm_rows[2] = {0, 0};
     int cgm_seg[2] = {0, 0};
+    // neither was set: one lattice, a cut per number of right-hand sides (auto_cut; kept, rows 0 =
+    // not yet estimated, per [two-site hops][precision][right-hand sides]); a batch, batch_slices
+    bool cgm_auto[2] = {true, true};
+    mutable Cut acut[2][2][HMC_MAX_RHS + 1] = {};
     int cgb_march[2] = {1, 1};   // step B marches too (with step A's cut) [FP64, FP32]
     // partial sums the last launched kernel left per unit when its workgroup count is not the
     // CG launch shape's (a march); the next launch's control block takes it over
@@ -500,9 +509,11 @@ static size_t ws_layout(hmc_ctx* c, char* base) {
 static int clamp_bpr(int ntiles2, int max_bpr) { return ntiles2 < max_bpr ? ntiles2 : max_bpr; }
 
 // Partial slots a unit needs per kind: the most workgroups any kernel runs on it (the CG steps,
-// at most kMaxBpr; the preconditioner's tau pass, 4 column groups per FP64 group width).
+// at most kMaxBpr: the tile kernels' tiles, or the marches with bands of four rows and segments of
+// one slice; the preconditioner's tau pass, 4 column groups per FP64 group width).
 static int unit_slots(const Lat& l) {
-    return std::max(clamp_bpr(tiles2_host(l.vol), kMaxBpr), 4 * pc_groups(l.LL, kPcCols));
+    return std::max({clamp_bpr(tiles2_host(l.vol), kMaxBpr), 4 * pc_groups(l.LL, kPcCols),
+                     std::min(kMaxBpr, l.Lt * ((l.L + 3) / 4))});
 }
 
 // A unit's march cut: rows per band at most `rows` (and at most what one thread per element, or
@@ -560,6 +571,25 @@ static int slice_threads(const SliceCut& sc, int L) {
     return std::min(kPcBlock, (sc.spw * L * (L / r) + 63) / 64 * 64);
 }
 
+// Slices per segment of a batch's marches when none were set: eight, or the most that leave
+// kBatchWgs workgroups over all units (two per CU).  Two chains of 24 x 24 x 80 and 12 x 12 x 40, one
+// vector each, are 40 workgroups of eight slices: 31 us an iteration against 16 with one.
+constexpr int kBatchWgs = 512;
+static int batch_slices(const hmc_ctx* c, int pi) {
+    if (!c->cgm_auto[pi]) return c->cgm_seg[pi];
+    for (int seg : {8, 6, 4, 3, 2}) {
+        long long wgs = 0;
+        for (const Lat& l : c->bi.lats) {
+            int parts, threads;
+            size_t lds;
+            (void)batch_march_plan(l, c->cgm_rows[pi], seg, pi == 1, unit_slots(l), parts, threads, lds);
+            wgs += (long long)parts * c->bi.nrhs;
+        }
+        if (wgs >= kBatchWgs) return seg;
+    }
+    return 1;
+}
+
 // Batch: (re)write the unit and block tables of one precision's launch shape, with the march
 // cuts of step A (this precision) and of the reliable update (FP64).
 static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
@@ -570,6 +600,7 @@ static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
     b.mthreads[pi] = b.rthreads[pi] = 0;
     b.mlds[pi] = b.rlds[pi] = 0;
     int part = 0;
+    const int seg = batch_slices(c, pi), rseg = batch_slices(c, 0);
     for (int ch = 0; ch < b.nchains; ++ch) {
         const Lat& lat = b.lats[size_t(ch)];
         for (int k = 0; k < b.nrhs; ++k) {
@@ -587,12 +618,12 @@ static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
             for (int w = 0; w < d.bpr; ++w) blocks.push_back(make_int2(u, w));
             int th = 0;
             size_t lds = 0;
-            d.mp = batch_march_plan(lat, c->cgm_rows[pi], c->cgm_seg[pi], pi == 1, unit_slots(lat), d.mparts, th, lds);
+            d.mp = batch_march_plan(lat, c->cgm_rows[pi], seg, pi == 1, unit_slots(lat), d.mparts, th, lds);
             m_ok = m_ok && d.mparts > 0;
             b.mthreads[pi] = std::max(b.mthreads[pi], th);
             b.mlds[pi] = std::max(b.mlds[pi], lds);
             for (int w = 0; w < d.mparts; ++w) mblocks.push_back(make_int2(u, w));
-            d.rmp = batch_march_plan(lat, c->cgm_rows[0], c->cgm_seg[0], false, unit_slots(lat), d.rparts, th, lds);
+            d.rmp = batch_march_plan(lat, c->cgm_rows[0], rseg, false, unit_slots(lat), d.rparts, th, lds);
             r_ok = r_ok && d.rparts > 0;
             b.rthreads[pi] = std::max(b.rthreads[pi], th);
             b.rlds[pi] = std::max(b.rlds[pi], lds);
@@ -765,6 +796,61 @@ struct Launch {
     size_t bm_lds = 0, br_lds = 0;
 };
 
+// The march cut of a solve of n right-hand sides on one lattice, when none was set: the rows per
+// band and slices per segment with the least estimated time of steps A and B.  A march of s slices
+// takes its launch, s + 1 dependent steps per round of workgroups, the memory traffic (with the
+// rows beside each band and the slice after each segment) and, when the workgroups do not divide
+// evenly over the CUs, the traffic of the busiest CU.  The coefficients (us, MB) are a fit to 1,500
+// cuts of 22 lattices from 8 x 8 x 16 to 80 x 80 x 200 with 1, 2 and 4 right-hand sides, where its choice
+// takes 1.02x the best cut's time on average (at worst 1.1x FP32, 1.3x FP64).  kDefaultRows x 8
+// slices, right where the lattice fills the chip, stays unless the estimate is a tenth below it: at 80 x 80 x 200
+// both ways take 69 us (FP32) and 138 us (FP64), while 20 x 20 x 100 goes from 29.8 to 12.7 us, 40 x 40 x 100 from
+// 33.2 to 16.1, and in FP64 40 x 40 x 100 with two right-hand sides from 48.0 to 38.0, 60 x 60 x 160 from
+// 74.0 to 60.2 us per iteration: eight slices in sequence on a few workgroups left most CUs idle.
+constexpr int kDefaultRows[2] = {4, 8};   // [FP64, FP32]
+constexpr int kDefaultSlices = 8;
+static Cut auto_cut(int L, int Lt, int n, int pi, int H, int slots) {
+    static const double coef[2][5] = {{8.0, 1.3, 0.063, 0.025, 0.41}, {7.4, 1.8, 0.064, 0.026, 0.26}};
+    static const int segs[] = {1, 2, 3, 4, 6, 8, 10, 12};
+    const double* k = coef[pi];
+    const int per_row = pi ? L / 2 : L;
+    const int top = std::min(L, kMarchCgThreads / per_row - 2 * H);
+    auto estimate = [&](int R, int s) {
+        const MarchPlan mp = make_march_plan(L, Lt, R, s);
+        const long long wgs = (long long)mp.nband * mp.nseg * n;
+        const int waves = ((mp.R + 2 * H) * per_row + 63) / 64, resident = std::max(1, 12 / waves);
+        const long long busy = (wgs + 255) / 256, rounds = (busy + resident - 1) / resident;
+        // bytes per site: r (z), p and t with the rows beside the band and the next slice, the
+        // stores, phi and every second iteration's solution update
+        const double reals = 24.0 * (mp.R + 2 * H) / mp.R + 24.0 / mp.seglen + 50.0, mb = reals * (pi ? 4 : 8) * 1e-6;
+        return k[0] + k[1] * double(rounds * (mp.seglen + 1)) + k[2] * mb * L * L * Lt * n +
+               k[3] * mb * 256.0 * double(busy * mp.seglen) * mp.R * L + k[4] * double(wgs) / 256.0;
+    };
+    const Cut dflt{std::max(1, std::min(kDefaultRows[pi], top)), kDefaultSlices};
+    Cut best = dflt;
+    double least = 0.9 * estimate(dflt.rows, dflt.slices);
+    for (int R = 1; R <= top; ++R)
+        for (int s : segs) {
+            const MarchPlan mp = make_march_plan(L, Lt, R, s);
+            const size_t lds = size_t(2) * (mp.R + 2 * H) * 4 * L * (pi ? sizeof(float2) : sizeof(double2));
+            if (mp.nband * mp.nseg > slots || lds > (size_t(64) << 10) || s > Lt) continue;
+            const double t = estimate(R, s);
+            if (t < least) {
+                least = t;
+                best = Cut{R, s};
+            }
+        }
+    return best;
+}
+// The cut in use in precision pi for n right-hand sides (rows 0: the tile kernels).
+static Cut cut_of(const hmc_ctx* c, int pi, int n) {
+    if (!c->cgm_auto[pi]) return Cut{c->cgm_rows[pi], c->cgm_seg[pi]};
+    const int nn2 = c->cf64.nn2 ? 1 : 0;
+    Cut& kept = c->acut[nn2][pi][std::min(n, HMC_MAX_RHS)];
+    if (kept.rows == 0) kept = auto_cut(c->L, c->Lt, n, pi, 1 + nn2, c->pstride);
+    return kept;
+}
+
 template <typename R>
 static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
     const int pi = sizeof(R) == sizeof(float) ? 1 : 0;
@@ -791,13 +877,14 @@ static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
     // thread each (at most kMarchCgThreads); slices per segment for about one workgroup per
     // compute unit over all right-hand sides (at least 2)
     // (the production model's two-site hops need two rows beside the band on either side)
-    if (c->cgm_rows[pi] > 0) {
+    const Cut cut = cut_of(c, pi, n), rcut = pi ? cut_of(c, 0, n) : cut;
+    if (cut.rows > 0) {
         const int per_row = pi ? c->L / 2 : c->L, H = l.nn2 ? 2 : 1;
-        const int rows = std::max(1, std::min(c->cgm_rows[pi], kMarchCgThreads / per_row - 2 * H));
+        const int rows = std::max(1, std::min(cut.rows, kMarchCgThreads / per_row - 2 * H));
         const size_t lds = march_cg_lds<R>(rows + 2 * H - 2, c->L);
         if (rows >= 1 && (rows + 2 * H) * per_row <= kMarchCgThreads && lds <= (size_t(64) << 10)) {
             const int nband = (c->L + std::min(rows, c->L) - 1) / std::min(rows, c->L);
-            int seg = c->cgm_seg[pi];
+            int seg = cut.slices;
             if (seg <= 0) seg = std::max(2, (c->Lt * nband * n + 255) / 256);
             l.cgm = make_march_plan(c->L, c->Lt, rows, seg);
             l.cgm_per_unit = l.cgm.nband * l.cgm.nseg;
@@ -808,12 +895,12 @@ static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
     }
     // the reliable update's FP64 marches: one thread per element of the band and its two
     // neighbour rows, as the FP64 step-A march
-    if (l.cgm_per_unit > 0 && c->cgm_rows[0] > 0 && !l.nn2) {
-        const int rows = std::max(1, std::min(c->cgm_rows[0], kMarchCgThreads / c->L - 2));
+    if (l.cgm_per_unit > 0 && rcut.rows > 0 && !l.nn2) {
+        const int rows = std::max(1, std::min(rcut.rows, kMarchCgThreads / c->L - 2));
         const size_t lds = march_cg_lds<double>(rows, c->L);
         if ((rows + 2) * c->L <= kMarchCgThreads && lds <= (size_t(64) << 10)) {
             const int nband = (c->L + std::min(rows, c->L) - 1) / std::min(rows, c->L);
-            int seg = c->cgm_seg[0];
+            int seg = rcut.slices;
             if (seg <= 0) seg = std::max(2, (c->Lt * nband * n + 255) / 256);
             l.rum = make_march_plan(c->L, c->Lt, rows, seg);
             l.rum_per_unit = l.rum.nband * l.rum.nseg;
@@ -1921,6 +2008,7 @@ static void apply_choice(hmc_ctx* c, const TuneChoice& ch) {
     for (int pi = 0; pi < 2; ++pi) {
         c->cgm_rows[pi] = ch.mrows[pi];
         c->cgm_seg[pi] = ch.mseg[pi];
+        c->cgm_auto[pi] = false;
         c->cgb_march[pi] = ch.mb[pi];
     }
     c->generation += 1;
@@ -1960,8 +2048,11 @@ static int autotune_common(hmc_ctx* c, const double* phi, const double2* b, int 
         if (prec == HMC_MIXED && c->p.reliable_every < 1) c->p.reliable_every = 50;
         double best = 1e300;
         int best_bpr = 0, last = -1;
-        // the workgroup count is tuned on the tile kernels, then the march shapes with it
+        // the workgroup count is tuned on the tile kernels, then the march shapes with it (the
+        // automatic cut among them)
+        const Cut own = c->is_batch ? Cut{0, 0} : auto_cut(c->L, c->Lt, n, pi, c->cf64.nn2 ? 2 : 1, c->pstride);
         c->cgm_rows[pi] = 0;
+        c->cgm_auto[pi] = false;
         c->generation += 1;
         for (int cb : cand) {
             const int bpr = clamp_bpr(maxt, cb);
@@ -2012,12 +2103,15 @@ static int autotune_common(hmc_ctx* c, const double* phi, const double2* b, int 
                 if (rc == HMC_OK && pi == 0) rc = upload_batch_shape(c, 1, c->bpr32);
                 return rc;
             };
-            for (int a = 0; a < nr && result == HMC_OK; ++a) {
-                if (!c->is_batch && ((rows[a] + (c->cf64.nn2 ? 4 : 2)) * per_row > kMarchCgThreads || rows[a] > c->L))
+            for (int a = own.rows > 0 ? -1 : 0; a < nr && result == HMC_OK; ++a) {
+                if (a >= 0 && !c->is_batch &&
+                    ((rows[a] + (c->cf64.nn2 ? 4 : 2)) * per_row > kMarchCgThreads || rows[a] > c->L))
                     continue;
-                for (int q = 0; q < ns && result == HMC_OK; ++q) {
+                for (int q = 0; q < (a < 0 ? 1 : ns) && result == HMC_OK; ++q) {
                     if (out->mtried[pi] >= HMC_TUNE_MARCH_MAX) break;
-                    result = apply_march(rows[a], segs[q]);
+                    const Cut cand = a < 0 ? own : Cut{rows[a], segs[q]};
+                    if (a >= 0 && cand.rows == own.rows && cand.slices == own.slices) continue;   // timed already
+                    result = apply_march(cand.rows, cand.slices);
                     if (result) break;
                     if (c->is_batch && c->bi.mgrid[pi] == 0) continue;     // no lattice of the batch marches
                     float ms = 0.f;
@@ -2033,13 +2127,13 @@ static int autotune_common(hmc_ctx* c, const double* phi, const double2* b, int 
                     out->candidates += 1;
                     const double us = 1e3 * ms / iters;
                     const int j = out->mtried[pi]++;
-                    out->mtried_rows[pi][j] = rows[a];
-                    out->mtried_slices[pi][j] = segs[q];
+                    out->mtried_rows[pi][j] = cand.rows;
+                    out->mtried_slices[pi][j] = cand.slices;
                     out->mtried_us[pi][j] = us;
                     if (us < best) {
                         best = us;
-                        best_r = rows[a];
-                        best_s = segs[q];
+                        best_r = cand.rows;
+                        best_s = cand.slices;
                     }
                 }
             }
@@ -2078,9 +2172,11 @@ static int autotune_common(hmc_ctx* c, const double* phi, const double2* b, int 
     (void)hipEventDestroy(e1);
     c->p = saved;
     if (result != HMC_OK) {
-        c->cgm_rows[0] = 4;
-        c->cgm_rows[1] = 8;
-        c->cgm_seg[0] = c->cgm_seg[1] = 8;
+        for (int pi = 0; pi < 2; ++pi) {
+            c->cgm_rows[pi] = kDefaultRows[pi];
+            c->cgm_seg[pi] = kDefaultSlices;
+            c->cgm_auto[pi] = true;
+        }
         c->cgb_march[0] = 1;
         c->cgb_march[1] = 1;
         (void)set_cg_shape(c, HMC_FP64, kDefaultBpr64);
@@ -2518,10 +2614,8 @@ int hmc_create(int L, int Lt, double dtau, const hmc_params* params, hmc_ctx** o
                           reinterpret_cast<const void*>(&k_mdm_march<kMdmMarchThreads>)})
         (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
     (void)hipGetLastError();
-    // step A marches by default (the tile kernels where a lattice's band does not fit)
-    c->cgm_rows[0] = 4;
-    c->cgm_rows[1] = 8;
-    c->cgm_seg[0] = c->cgm_seg[1] = 8;
+    // step A marches by default, cut by auto_cut (the tile kernels where a lattice's band does not
+    // fit)
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tuned.find(TuneKey{L, Lt, c->cap, c->device, c->cf64.nn2 != 0});
@@ -2706,6 +2800,7 @@ int hmc_set_cg_march(hmc_ctx* c, int precision, int rows, int slices) {
         if (precision == -1 || precision == (pi ? HMC_MIXED : HMC_FP64)) {
             c->cgm_rows[pi] = rows;
             c->cgm_seg[pi] = slices;
+            c->cgm_auto[pi] = false;
         }
     c->generation += 1;   // captured graphs hold the launch shape
     return HMC_OK;
@@ -2730,8 +2825,9 @@ int hmc_get_cg_march(const hmc_ctx* c, int precision, int* rows, int* slices) {
     if (c == nullptr || rows == nullptr || slices == nullptr) return fail(HMC_ERR_INVALID_ARG, "NULL argument");
     if (precision != HMC_FP64 && precision != HMC_MIXED) return fail(HMC_ERR_INVALID_ARG, "unknown precision");
     const int pi = precision == HMC_MIXED ? 1 : 0;
-    *rows = c->cgm_rows[pi];
-    *slices = c->cgm_seg[pi];
+    const Cut cut = cut_of(c, pi, c->cap);
+    *rows = cut.rows;
+    *slices = cut.slices;
     return HMC_OK;
 }
 
@@ -3227,9 +3323,10 @@ int hmc_batch_create(int nchains, const int* L, const int* L_tau, const double* 
     c->bpr32 = kDefaultBpr32;
     // step A and the reliable update march by default (row caps per band; every lattice takes
     // the rows its band allows, or the tile kernels if some lattice fits no cut)
-    c->cgm_rows[0] = 4;
-    c->cgm_rows[1] = 8;
-    c->cgm_seg[0] = c->cgm_seg[1] = 8;
+    for (int pi = 0; pi < 2; ++pi) {
+        c->cgm_rows[pi] = kDefaultRows[pi];
+        c->cgm_seg[pi] = kDefaultSlices;
+    }
     {
         TuneChoice ch;
         if (tune_cache_lookup(tune_key(c), ch)) apply_choice(c, ch);
@@ -3293,6 +3390,7 @@ int hmc_batch_set_cg_march(hmc_batch* hb, int precision, int rows, int slices) {
         if (precision == -1 || precision == (pi ? HMC_MIXED : HMC_FP64)) {
             c->cgm_rows[pi] = rows;
             c->cgm_seg[pi] = slices;
+            c->cgm_auto[pi] = false;
         }
     c->generation += 1;
     int rc = upload_batch_shape(c, 0, c->bpr64);
