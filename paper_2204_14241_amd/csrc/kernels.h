@@ -274,131 +274,147 @@ __device__ __forceinline__ double* part_slot(const CgCtl& c, int kind, const UPo
     return c.part + size_t(kind - 1) * c.nslots + p.part;
 }
 
-constexpr int kStateWords = int(sizeof(CgState) / 4);
-static_assert(sizeof(CgState) % 4 == 0 && kStateWords <= kBlock, "state record layout");
+static_assert(sizeof(CgState) % 8 == 0, "state record layout");
 
-// The workgroup's copy of its right-hand side's record (one per kernel).
-__device__ __forceinline__ CgState& cg_shared() {
-    __shared__ CgState sh;
-    return sh;
+// Sum of n partials in a fixed order, by every wavefront for itself (lane j takes partials j, j + 64,
+// ... and the lanes are added in a butterfly), so that every thread of every workgroup holds the
+// bit-identical total and no barrier is needed.  Eight loads are in flight per lane.
+__device__ __forceinline__ double lane_partials(const double* __restrict__ p, int n) {
+    const int lane = threadIdx.x & 63;
+    double v = 0.0;
+    for (int j0 = lane; j0 < n; j0 += 8 * 64) {
+        double w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) w[u] = j0 + u * 64 < n ? p[j0 + u * 64] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += w[u];
+    }
+    return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
 }
 
 // Reduce the pending partials of right-hand side k (nparts of them, as many as the producing
-// kernel ran workgroups on the unit) and advance its state machine into cg_shared().  Every
-// workgroup computes the same record (deterministic order).  The record (one dword per lane)
-// and the partials the host expects to be pending are loaded in the same memory round trip;
-// the partials are used only if the record says so.  Returns the kind consumed (PEND_NONE if
-// nothing was pending).  A pending kind other than the expected one (a sequencing error of
-// the host) fails the right-hand side instead of using foreign partials.
-__device__ __forceinline__ int cg_finalize(const CgCtl& c, const UPos& pos, int nparts) {
+// kernel ran workgroups on the unit) and advance its state machine into s.  Every thread computes
+// the same record (deterministic order).  The record and the partials the host expects to be
+// pending are loaded in the same memory round trip; the partials are used only if the record says
+// so.  Returns the kind consumed (PEND_NONE if nothing was pending).  A pending kind other than the
+// expected one (a sequencing error of the host) fails the right-hand side instead of using foreign
+// partials.
+//
+// Every kernel of a solve starts with this, so its latency bounds small lattices: without a copy of
+// the record in LDS it needs no barrier (there were five, and one thread ran the state machine).
+__device__ __forceinline__ int cg_finalize(const CgCtl& c, const UPos& pos, int nparts, CgState& s) {
     const int k = pos.k;
-    CgState& sh = cg_shared();
-    __shared__ int consumed;
-    const int t = threadIdx.x;
-    unsigned w = 0u;
-    if (t < kStateWords) w = reinterpret_cast<const unsigned*>(c.st_in + k)[t];
-    double tot = 0.0;
+    double mine = 0.0;
     if (c.expect != PEND_NONE) {
         const int np = c.nparts > 0 ? c.nparts
                        : c.nparts == kPartsMarch ? pos.mparts
                        : c.nparts == kPartsRu ? pos.rparts : nparts;
-        tot = sum_partials(part_slot(c, c.expect, pos), np);
+        mine = lane_partials(part_slot(c, c.expect, pos), np);
     }
-    if (t < kStateWords) reinterpret_cast<unsigned*>(&sh)[t] = w;
-    __syncthreads();
-    if (t == 0) {
-        CgState& s = sh;
-        consumed = s.pending;
-        if (s.pending != PEND_NONE && s.pending != c.expect) {
-            s.mode = CG_FAILED;
-        } else {
-            switch (s.pending) {
-                case PEND_BB:
-                    s.bb = tot;
-                    s.stop_rr = s.tol2 * tot;
-                    s.rr = s.rr_prev = s.rr_true = tot;
-                    s.rz = s.rz_prev = tot;
-                    s.ru_rr = s.drop2 * tot;
-                    s.zinit = 1;
-                    s.zstage = 0;
-                    s.mode = !finite(tot) ? CG_FAILED : (tot > 0.0 ? CG_ACTIVE : CG_DONE);
-                    break;
-                case PEND_TT:
-                    if (s.mode == CG_ACTIVE) {
-                        if (!(tot > 0.0) || !finite(tot)) s.mode = CG_FAILED;
-                        else s.alpha_cur = s.rz / tot;
-                    }
-                    break;
-                case PEND_RR:
-                    if (s.mode == CG_ACTIVE) {
-                        if (!finite(tot)) {
-                            s.mode = CG_FAILED;
-                        } else {
-                            s.rz_prev = s.rz;
-                            if (!s.pc) {
-                                s.beta = tot / s.rz;
-                                s.rz = tot;
-                            }
-                            s.rr_prev = s.rr;
-                            s.rr = tot;
-                            s.alpha = s.alpha_cur;
-                            s.iters += 1;
-                            if (tot <= s.stop_rr || tot <= s.ru_rr) s.mode = CG_CONV_ITER;
-                            else if (s.iters >= s.maxit) s.mode = CG_MAXIT;
-                        }
-                    }
-                    break;
-                case PEND_RU:
-                    s.rr_true = tot;
-                    s.n_ru += 1;
-                    s.alpha = 0.0;
-                    s.alpha_old = 0.0;
+    s = c.st_in[k];
+    asm volatile("" : "+v"(mine));    // the partials are loaded whether or not the record wants them
+    const int consumed = s.pending;
+    if (consumed == PEND_NONE) return PEND_NONE;
+    if (consumed != c.expect) {
+        s.mode = CG_FAILED;
+    } else {
+        const double tot = wave_sum(mine);
+        switch (consumed) {
+            case PEND_BB:
+                s.bb = tot;
+                s.stop_rr = s.tol2 * tot;
+                s.rr = s.rr_prev = s.rr_true = tot;
+                s.rz = s.rz_prev = tot;
+                s.ru_rr = s.drop2 * tot;
+                s.zinit = 1;
+                s.zstage = 0;
+                s.mode = !finite(tot) ? CG_FAILED : (tot > 0.0 ? CG_ACTIVE : CG_DONE);
+                break;
+            case PEND_TT:
+                if (s.mode == CG_ACTIVE) {
+                    if (!(tot > 0.0) || !finite(tot)) s.mode = CG_FAILED;
+                    else s.alpha_cur = s.rz / tot;
+                }
+                break;
+            case PEND_RR:
+                if (s.mode == CG_ACTIVE) {
                     if (!finite(tot)) {
                         s.mode = CG_FAILED;
-                    } else if (tot <= s.stop_rr) {
-                        s.mode = CG_DONE;
-                    } else if (s.mode == CG_MAXIT) {
-                        s.mode = CG_STOPPED;
                     } else {
+                        s.rz_prev = s.rz;
                         if (!s.pc) {
-                            s.beta = tot / s.rz_prev;
+                            s.beta = tot / s.rz;
                             s.rz = tot;
                         }
+                        s.rr_prev = s.rr;
                         s.rr = tot;
-                        s.ru_rr = s.drop2 * tot;
-                        s.mode = CG_ACTIVE;
+                        s.alpha = s.alpha_cur;
+                        s.iters += 1;
+                        if (tot <= s.stop_rr || tot <= s.ru_rr) s.mode = CG_CONV_ITER;
+                        else if (s.iters >= s.maxit) s.mode = CG_MAXIT;
                     }
-                    break;
-                case PEND_RZ:
-                    if (s.mode == CG_ACTIVE) {
-                        if (!(tot > 0.0) || !finite(tot)) {
-                            s.mode = CG_FAILED;
-                        } else if (s.zinit) {
-                            s.beta = 0.0;
-                            s.rz = tot;
-                            s.zinit = 0;
-                        } else {
-                            s.beta = tot / s.rz_prev;
-                            s.rz = tot;
-                        }
+                }
+                break;
+            case PEND_RU:
+                s.rr_true = tot;
+                s.n_ru += 1;
+                s.alpha = 0.0;
+                s.alpha_old = 0.0;
+                if (!finite(tot)) {
+                    s.mode = CG_FAILED;
+                } else if (tot <= s.stop_rr) {
+                    s.mode = CG_DONE;
+                } else if (s.mode == CG_MAXIT) {
+                    s.mode = CG_STOPPED;
+                } else {
+                    if (!s.pc) {
+                        s.beta = tot / s.rz_prev;
+                        s.rz = tot;
                     }
-                    s.zstage = 0;
-                    break;
-            }
+                    s.rr = tot;
+                    s.ru_rr = s.drop2 * tot;
+                    s.mode = CG_ACTIVE;
+                }
+                break;
+            case PEND_RZ:
+                if (s.mode == CG_ACTIVE) {
+                    if (!(tot > 0.0) || !finite(tot)) {
+                        s.mode = CG_FAILED;
+                    } else if (s.zinit) {
+                        s.beta = 0.0;
+                        s.rz = tot;
+                        s.zinit = 0;
+                    } else {
+                        s.beta = tot / s.rz_prev;
+                        s.rz = tot;
+                    }
+                }
+                s.zstage = 0;
+                break;
         }
-        s.pending = PEND_NONE;
     }
-    __syncthreads();
+    s.pending = PEND_NONE;
     return consumed;
 }
 
-// Workgroup 0 of a right-hand side publishes the record for the next kernel (all threads
-// of the workgroup call this; changes made by thread 0 before it are included).
-__device__ __forceinline__ void cg_publish(const CgCtl& c, const UPos& pos) {
-    __syncthreads();
-    if (pos.blk == 0 && threadIdx.x < kStateWords)
-        reinterpret_cast<unsigned*>(c.st_out + pos.k)[threadIdx.x] =
-            reinterpret_cast<const unsigned*>(&cg_shared())[threadIdx.x];
+// Workgroup 0 of a right-hand side publishes the record for the next kernel (which is the first to
+// read it, so this may come as soon as the record's new contents are known).
+__device__ __forceinline__ void cg_publish(const CgCtl& c, const UPos& pos, const CgState& s) {
+    if (pos.blk == 0 && threadIdx.x == 0) c.st_out[pos.k] = s;
+}
+// What step A leaves: the direction buffers change places, its |t|^2 partials are pending, and the
+// step still to be added to x is deferred, or with an older one pending both are added now.
+__device__ __forceinline__ void cg_publish_a(const CgCtl& c, const UPos& pos, CgState s) {
+    s.alpha_old = s.alpha_old != 0.0 ? 0.0 : s.alpha;
+    s.alpha = 0.0;
+    s.pbuf = 1 - s.pbuf;
+    s.pending = PEND_TT;
+    cg_publish(c, pos, s);
 }
 
 // ------------------------------------------------------------------------------------
@@ -527,16 +543,16 @@ __global__ __launch_bounds__(kBlock) void k_cg_a(CgCtl ctl, Geo geo, CgVecs<R> v
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
     const R* phi = phi_base + pos.phioff;
-    cg_finalize(ctl, pos, pos.bpr);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, pos.bpr, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const R alpha = R(S.alpha), alpha_old = R(S.alpha_old), beta = R(S.beta);
     const bool fold = S.alpha_old != 0.0;
-    const double defer = S.alpha;
     const int pb = S.pbuf;
+    cg_publish_a(ctl, pos, S);
     const size_t off = pos.voff;
     const C2<R>* pin = (pb ? v.p1 : v.p0) + off;
     C2<R>* pout = (pb ? v.p0 : v.p1) + off;
@@ -570,14 +586,6 @@ __global__ __launch_bounds__(kBlock) void k_cg_a(CgCtl ctl, Geo geo, CgVecs<R> v
         }
     }
     store_partial(ctl, PEND_TT, pos, part);
-    if (threadIdx.x == 0) {
-        CgState& W = cg_shared();
-        W.alpha_old = fold ? 0.0 : defer;
-        W.alpha = 0.0;
-        W.pbuf = 1 - pb;
-        W.pending = PEND_TT;
-    }
-    cg_publish(ctl, pos);
 }
 
 // CG step B:  r -= alpha_k M^dagger t;  partial |r|^2.
@@ -587,13 +595,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_b(CgCtl ctl, Geo geo, CgVecs<R> v
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
     const R* phi = phi_base + pos.phioff;
-    cg_finalize(ctl, pos, pos.bpr);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, pos.bpr, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const R alpha = R(S.alpha_cur);
+    S.pending = PEND_RR;
+    cg_publish(ctl, pos, S);
     const size_t off = pos.voff;
     SrcPlain<R> src{v.t + off, lat.vol};
     C2<R>* r = v.r + off;
@@ -617,8 +627,6 @@ __global__ __launch_bounds__(kBlock) void k_cg_b(CgCtl ctl, Geo geo, CgVecs<R> v
         }
     }
     store_partial(ctl, PEND_RR, pos, part);
-    if (threadIdx.x == 0) cg_shared().pending = PEND_RR;
-    cg_publish(ctl, pos);
 }
 
 // Reliable update, part 1 (elementwise): fold the pending steps into the FP64 solution,
@@ -629,16 +637,19 @@ __global__ __launch_bounds__(kBlock) void k_ru_fold(CgCtl ctl, Geo geo, double2*
                                                     CgVecs<R> v, int filter) {
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
-    cg_finalize(ctl, pos, pos.bpr);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, pos.bpr, S);
     if (!((1 << S.mode) & filter)) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const double alpha = S.alpha, alpha_old = S.alpha_old;
+    const int pb = S.pbuf;
+    S.alpha = S.alpha_old = 0.0;
+    cg_publish(ctl, pos, S);
     const size_t off = pos.voff;
-    const C2<R>* p = (S.pbuf ? v.p1 : v.p0) + off;
-    const C2<R>* q = (S.pbuf ? v.p0 : v.p1) + off;   // the previous direction
+    const C2<R>* p = (pb ? v.p1 : v.p0) + off;
+    const C2<R>* q = (pb ? v.p0 : v.p1) + off;   // the previous direction
     const bool separate = (void*)v.x != (void*)x64, both = alpha_old != 0.0;
     for (TileSpan sp = tile_span(pos.blk, pos.bpr, tiles1(lat)); sp.first < sp.end; sp.first += sp.step) {
         const int tile = sp.first;
@@ -665,9 +676,6 @@ __global__ __launch_bounds__(kBlock) void k_ru_fold(CgCtl ctl, Geo geo, double2*
             x64[i] = xv;
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) cg_shared().alpha = cg_shared().alpha_old = 0.0;
-    cg_publish(ctl, pos);
 }
 
 // Reliable update, part 2: t64 = M x64 (FP64) for right-hand sides in `filter`.
@@ -679,10 +687,10 @@ __global__ __launch_bounds__(kBlock) void k_ru_apply(CgCtl ctl, Geo geo, const d
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
     const double* phi = phi_base + pos.phioff;
-    cg_finalize(ctl, pos, pos.bpr);
-    const int mode = cg_shared().mode;
-    cg_publish(ctl, pos);
-    if (!((1 << mode) & filter)) return;
+    CgState S;
+    cg_finalize(ctl, pos, pos.bpr, S);
+    cg_publish(ctl, pos, S);
+    if (!((1 << S.mode) & filter)) return;
     const size_t off = pos.voff;
     SrcPlain<double> src{x64 + off, lat.vol};
     for (TileSpan sp = tile_span(pos.blk, pos.bpr, tiles1(lat)); sp.first < sp.end; sp.first += sp.step) {
@@ -708,11 +716,12 @@ __global__ __launch_bounds__(kBlock) void k_ru_resid(CgCtl ctl, Geo geo, const d
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
     const double* phi = phi_base + pos.phioff;
-    cg_finalize(ctl, pos, pos.bpr);
-    if (!((1 << cg_shared().mode) & filter)) {
-        cg_publish(ctl, pos);
-        return;
-    }
+    CgState S;
+    cg_finalize(ctl, pos, pos.bpr, S);
+    const bool work = ((1 << S.mode) & filter) != 0;
+    if (work) S.pending = PEND_RU;
+    cg_publish(ctl, pos, S);
+    if (!work) return;
     const size_t off = pos.voff;
     SrcPlain<double> src{t64 + off, lat.vol};
     double part = 0.0;
@@ -733,8 +742,6 @@ __global__ __launch_bounds__(kBlock) void k_ru_resid(CgCtl ctl, Geo geo, const d
         }
     }
     store_partial(ctl, PEND_RU, pos, part);
-    if (threadIdx.x == 0) cg_shared().pending = PEND_RU;
-    cg_publish(ctl, pos);
 }
 
 // CG start from x = 0: x64 = 0, r = b, both direction buffers and x_lo cleared, partial |b|^2.
@@ -765,17 +772,14 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(CgCtl ctl, Geo geo, const do
         }
     }
     store_partial(ctl, PEND_BB, pos, part);
-    if (threadIdx.x == 0) {
-        CgState& S = cg_shared();
-        S = CgState{};
-        S.tol2 = tol2;
-        S.drop2 = drop2;
-        S.maxit = maxit;
-        S.pc = pc;
-        S.mode = CG_ACTIVE;
-        S.pending = PEND_BB;
-    }
-    cg_publish(ctl, pos);
+    CgState S{};
+    S.tol2 = tol2;
+    S.drop2 = drop2;
+    S.maxit = maxit;
+    S.pc = pc;
+    S.mode = CG_ACTIVE;
+    S.pending = PEND_BB;
+    cg_publish(ctl, pos, S);
 }
 
 // One workgroup per right-hand side: reduce whatever is pending (nparts per unit: 0 selects
@@ -783,8 +787,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(CgCtl ctl, Geo geo, const do
 template <class Geo>
 __global__ __launch_bounds__(kBlock) void k_cg_finalize(CgCtl ctl, Geo geo, int nparts) {
     const UPos pos = geo.unit(blockIdx.x, 0);
-    cg_finalize(ctl, pos, nparts > 0 ? nparts : pos.bpr);
-    cg_publish(ctl, pos);
+    CgState S;
+    cg_finalize(ctl, pos, nparts > 0 ? nparts : pos.bpr, S);
+    cg_publish(ctl, pos, S);
 }
 
 // ------------------------------------------------------------------------------------
@@ -924,16 +929,16 @@ void k_cg_a2(CgCtl ctl, Geo geo, CgVecs<float> v, const float* __restrict__ phi_
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
     const float* phi = phi_base + pos.phioff;
-    cg_finalize(ctl, pos, pos.bpr);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, pos.bpr, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const float alpha = float(S.alpha), alpha_old = float(S.alpha_old), beta = float(S.beta);
     const bool fold = S.alpha_old != 0.0;
-    const double defer = S.alpha;
     const int pb = S.pbuf;
+    cg_publish_a(ctl, pos, S);
     const size_t off = pos.voff;
     const float2* pin = (pb ? v.p1 : v.p0) + off;
     float2* pout = (pb ? v.p0 : v.p1) + off;
@@ -967,14 +972,6 @@ void k_cg_a2(CgCtl ctl, Geo geo, CgVecs<float> v, const float* __restrict__ phi_
         }
     }
     store_partial(ctl, PEND_TT, pos, part);
-    if (threadIdx.x == 0) {
-        CgState& W = cg_shared();
-        W.alpha_old = fold ? 0.0 : defer;
-        W.alpha = 0.0;
-        W.pbuf = 1 - pb;
-        W.pending = PEND_TT;
-    }
-    cg_publish(ctl, pos);
 }
 
 // CG step B, FP32 pair form (same algebra as k_cg_b).
@@ -984,13 +981,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_b2(CgCtl ctl, Geo geo, CgVecs<flo
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
     const float* phi = phi_base + pos.phioff;
-    cg_finalize(ctl, pos, pos.bpr);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, pos.bpr, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const float alpha = float(S.alpha_cur);
+    S.pending = PEND_RR;
+    cg_publish(ctl, pos, S);
     const size_t off = pos.voff;
     SrcPlain2 src{v.t + off, lat.vol};
     float2* r = v.r + off;
@@ -1014,8 +1013,6 @@ __global__ __launch_bounds__(kBlock) void k_cg_b2(CgCtl ctl, Geo geo, CgVecs<flo
         }
     }
     store_partial(ctl, PEND_RR, pos, part);
-    if (threadIdx.x == 0) cg_shared().pending = PEND_RR;
-    cg_publish(ctl, pos);
 }
 
 // ------------------------------------------------------------------------------------

@@ -405,16 +405,16 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_a2_march(CgCtl ctl, MG m
         for (int c = 0; c < 4; ++c) rz[c] = ld4(z, size_t(c) * vol + size_t(t0) * LL + ro);
     }
     load_phi(t0);
-    cg_finalize(ctl, pos, w.nparts_in);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, w.nparts_in, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const float alpha = float(S.alpha), alpha_old = float(S.alpha_old), beta = float(S.beta);
     const bool fold = S.alpha_old != 0.0;   // x += both pending steps this iteration (see k_cg_a)
-    const double defer = S.alpha;
     const int pb = S.pbuf;
+    cg_publish_a(ctl, pos, S);
     const float2* pin = (pb ? v.p1 : v.p0) + off;
     float2* pout = (pb ? v.p0 : v.p1) + off;
     float2* x = v.x + off;
@@ -492,14 +492,6 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_a2_march(CgCtl ctl, MG m
         nxt = sw;
     }
     store_partial(ctl, PEND_TT, pos, part);
-    if (threadIdx.x == 0) {
-        CgState& W = cg_shared();
-        W.alpha_old = fold ? 0.0 : defer;
-        W.alpha = 0.0;
-        W.pbuf = 1 - pb;
-        W.pending = PEND_TT;
-    }
-    cg_publish(ctl, pos);
 }
 
 template <class MG, bool NN2>
@@ -539,16 +531,16 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_a_march(CgCtl ctl, MG mg
         for (int c = 0; c < 4; ++c) rz[c] = z[size_t(c) * vol + size_t(t0) * LL + ro];
     }
     load_phi(t0);
-    cg_finalize(ctl, pos, w.nparts_in);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, w.nparts_in, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const double alpha = S.alpha, alpha_old = S.alpha_old, beta = S.beta;
     const bool fold = alpha_old != 0.0;     // x += both pending steps this iteration (see k_cg_a)
-    const double defer = S.alpha;
     const int pb = S.pbuf;
+    cg_publish_a(ctl, pos, S);
     const double2* pin = (pb ? v.p1 : v.p0) + off;
     double2* pout = (pb ? v.p0 : v.p1) + off;
     double2* x = v.x + off;
@@ -623,14 +615,6 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_a_march(CgCtl ctl, MG mg
         nxt = sw;
     }
     store_partial(ctl, PEND_TT, pos, part);
-    if (threadIdx.x == 0) {
-        CgState& W = cg_shared();
-        W.alpha_old = fold ? 0.0 : defer;
-        W.alpha = 0.0;
-        W.pbuf = 1 - pb;
-        W.pending = PEND_TT;
-    }
-    cg_publish(ctl, pos);
 }
 
 // ------------------------------------------------------------------------------------
@@ -692,13 +676,15 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_b2_march(CgCtl ctl, MG m
     // the first slice's loads do not depend on the record: in flight while it is reduced
     load_slab(t0);
     load_site(t0);
-    cg_finalize(ctl, pos, w.nparts_in);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, w.nparts_in, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const float alpha = float(S.alpha_cur);
+    S.pending = PEND_RR;
+    cg_publish(ctl, pos, S);
     double part = 0.0;
     for (int tau = t0; tau < t1; ++tau) {
         float2* cur = (tau - t0) & 1 ? buf1 : buf0;
@@ -730,8 +716,6 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_b2_march(CgCtl ctl, MG m
         }
     }
     store_partial(ctl, PEND_RR, pos, part);
-    if (threadIdx.x == 0) cg_shared().pending = PEND_RR;
-    cg_publish(ctl, pos);
 }
 
 template <class MG, bool NN2>
@@ -786,13 +770,15 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_b_march(CgCtl ctl, MG mg
     // the first slice's loads do not depend on the record: in flight while it is reduced
     load_slab(t0);
     load_site(t0);
-    cg_finalize(ctl, pos, w.nparts_in);
-    const CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, w.nparts_in, S);
     if (S.mode != CG_ACTIVE) {
-        cg_publish(ctl, pos);
+        cg_publish(ctl, pos, S);
         return;
     }
     const double alpha = S.alpha_cur;
+    S.pending = PEND_RR;
+    cg_publish(ctl, pos, S);
     double part = 0.0;
     for (int tau = t0; tau < t1; ++tau) {
         double2* cur = (tau - t0) & 1 ? buf1 : buf0;
@@ -824,8 +810,6 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_b_march(CgCtl ctl, MG mg
         }
     }
     store_partial(ctl, PEND_RR, pos, part);
-    if (threadIdx.x == 0) cg_shared().pending = PEND_RR;
-    cg_publish(ctl, pos);
 }
 
 // ------------------------------------------------------------------------------------
@@ -851,10 +835,10 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_apply_march(CgCtl ctl, M
     const UPos& pos = w.pos;
     const double* phi = phi_base + pos.phioff;
     const int L = lat.L, Lt = lat.Lt, LL = lat.LL, vol = lat.vol, rowc = 4 * L;
-    cg_finalize(ctl, pos, w.nparts_in);
-    const int mode = cg_shared().mode;
-    cg_publish(ctl, pos);
-    if (!((1 << mode) & filter)) return;
+    CgState S;
+    cg_finalize(ctl, pos, w.nparts_in, S);
+    cg_publish(ctl, pos, S);
+    if (!((1 << S.mode) & filter)) return;
     const size_t off = pos.voff;
     const double2* xin = x64 + off;
     double2* t = t64 + off;
@@ -937,11 +921,12 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_resid_march(CgCtl ctl, M
     const UPos& pos = w.pos;
     const double* phi = phi_base + pos.phioff;
     const int L = lat.L, Lt = lat.Lt, LL = lat.LL, vol = lat.vol, rowc = 4 * L;
-    cg_finalize(ctl, pos, w.nparts_in);
-    if (!((1 << cg_shared().mode) & filter)) {
-        cg_publish(ctl, pos);
-        return;
-    }
+    CgState S;
+    cg_finalize(ctl, pos, w.nparts_in, S);
+    const bool work = ((1 << S.mode) & filter) != 0;
+    if (work) S.pending = PEND_RU;
+    cg_publish(ctl, pos, S);
+    if (!work) return;
     const size_t off = pos.voff;
     const double2* tin = t64 + off;
     const double2* bb = b + off;
@@ -1012,8 +997,6 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_resid_march(CgCtl ctl, M
         }
     }
     store_partial(ctl, PEND_RU, pos, part);
-    if (threadIdx.x == 0) cg_shared().pending = PEND_RU;
-    cg_publish(ctl, pos);
 }
 
 // ------------------------------------------------------------------------------------

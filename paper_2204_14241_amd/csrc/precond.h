@@ -66,22 +66,20 @@ __global__ __launch_bounds__(kPcBlock) void k_pc_xy(CgCtl ctl, Geo geo, const C2
     const PcBlob bl = pc_blob_layout(L, lat.Lt);
     const double* B = blob + pos.pcoff;
     for (int i = threadIdx.x; i < L; i += blockDim.x) tw[i] = mk<R>(R(B[bl.twl + 2 * i]), R(B[bl.twl + 2 * i + 1]));
-    const int got = cg_finalize(ctl, pos, nparts);   // ends with a barrier
-    CgState& S = cg_shared();
+    CgState S;
+    const int got = cg_finalize(ctl, pos, nparts, S);
     const bool work = S.pc && S.mode == CG_ACTIVE &&
                       (INV ? got == PEND_RZ : (got == PEND_RR || got == PEND_RU || got == PEND_BB));
-    if (!work) {
-        cg_publish(ctl, pos);
-        return;
-    }
-    if (!INV && threadIdx.x == 0) S.zstage = 1;
+    if (!INV && work) S.zstage = 1;
+    cg_publish(ctl, pos, S);
+    if (!work) return;
+    __syncthreads();
     const size_t o = pos.voff + size_t(s0) * LL;
     const C2<R>* in = src + o;
     C2<R>* out = dst + o;
     fft_slices<R, INV, MAXR>(
         ExDevice(), [&](int i) HMC_FLAT { return in[i]; }, buf, [&](int i, C2<R> v) HMC_FLAT { out[i] = v; }, ns, pos.sc.pitch,
         blob_plan(B, bl.planL), tw);
-    cg_publish(ctl, pos);
 }
 
 // Pass 2.  For the (x, y) frequency k of a column, K acts along tau as
@@ -324,13 +322,15 @@ void k_pc_t(CgCtl ctl, Geo geo, C2<R>* z,
     const UPos pos = geo.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = pos.lat;
     const int L = lat.L, Lt = lat.Lt, LL = lat.LL;
-    cg_finalize(ctl, pos, 0);
-    CgState& S = cg_shared();
+    CgState S;
+    cg_finalize(ctl, pos, 0, S);
     const bool work = S.pc && S.mode == CG_ACTIVE && S.zstage == 1;
-    if (!work) {
-        cg_publish(ctl, pos);
-        return;
+    if (work) {
+        S.zstage = 2;
+        S.pending = PEND_RZ;
     }
+    cg_publish(ctl, pos, S);
+    if (!work) return;
     const int ng = pc_groups(LL, kPcCols);
     const int comp = pos.blk / ng, grp = pos.blk - comp * ng;
     // the chunk is the wavefront's (a scalar), the column the lane's
@@ -381,11 +381,6 @@ void k_pc_t(CgCtl ctl, Geo geo, C2<R>* z,
         if (j < n && on) *at(j) = v[j];
     }
     store_partial(ctl, PEND_RZ, pos, part / double(LL));
-    if (threadIdx.x == 0) {
-        S.zstage = 2;
-        S.pending = PEND_RZ;
-    }
-    cg_publish(ctl, pos);
 }
 
 }  // namespace hmc
