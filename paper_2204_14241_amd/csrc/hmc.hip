@@ -71,7 +71,7 @@ int fail(int code, const char* fmt, ...) {
 
 size_t align_up(size_t n, size_t a) { return (n + a - 1) / a * a; }
 
-constexpr int kCheckEvery = 32;     // FP64 CG: iterations between host status reads
+constexpr int kCheckEvery = 32;     // FP64 CG: most iterations between host status reads
 constexpr int kSlots = 32;          // device scalars (energies, actions)
 constexpr int kChainSlots = 8;      // per-lattice scalars in batch mode
 constexpr int kDefaultBpr64 = 1024; // default CG workgroups per right-hand side, FP64
@@ -965,6 +965,15 @@ template <> struct KrylovBufs<float> {
     static Coef<float> cf(hmc_ctx* c) { return c->cf32; }
 };
 
+// About how many more iterations a unit needs, from its mean rate of convergence so far (the
+// iterated |r|^2 against |b|^2).
+static int iterations_left(const CgState& h) {
+    if (h.mode != CG_ACTIVE || h.iters < 1) return 1;
+    const double fallen = std::log(h.bb / h.rr), to_go = std::log(h.rr / h.stop_rr);
+    if (!(fallen > 0.0) || !(to_go > 0.0)) return to_go > 0.0 ? 1 << 20 : 1;
+    return int(std::min(1e6, 1.0 + to_go * h.iters / fallen));
+}
+
 static bool finished(int mode) { return mode == CG_DONE || mode == CG_STOPPED || mode == CG_FAILED; }
 
 // Control block for the next CG launch; advances the state-record parity.
@@ -1352,64 +1361,97 @@ static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64,
         for (int j = 0; j < n; ++j) done_early = done_early && finished(c->h_st[j].mode);
     }
 
-    const int nlaunch = chunk_launches(chunk, lc.pc);
     int issued = k0 * chunk;
     int k = k0;
     bool have_prev = false;
     const int kt_a = mixed ? 0 : 2;
     const bool sample = c->timing && !use_graphs;
     bool start_active_prev = true;   // were all units iterating when chunk k-1 began
-    // Chunks are issued one ahead of the status read, so the GPU never idles on the host;
-    // once every unit is finished the remaining launches return at once.
+    bool all = false;                // the last records read: every unit is finished
+    int left = 0;                    // ... and about how many iterations the others still need
+    const CgState* last = c->h_st;   // ... where they are
+    int size[2] = {chunk, chunk};    // iterations of the last two chunks
+    // Wait for chunk j's records.
+    auto settle = [&](int j) -> int {
+        HIPCHK(hipEventSynchronize(c->ev[j & 1]));
+        const CgState* hs = last = c->h_st + size_t(j & 1) * c->nunits;
+        bool all_active = true;
+        all = true;
+        left = 0;
+        for (int u = 0; u < n; ++u) {
+            all = all && finished(hs[u].mode);
+            all_active = all_active && hs[u].mode == CG_ACTIVE;
+            if (!finished(hs[u].mode)) left = std::max(left, iterations_left(hs[u]));
+        }
+        // chunk j began in the state chunk j-1 ended in; if every unit was iterating then and is
+        // still iterating at its end, its mid-chunk sample did full work
+        if (sample && start_active_prev && all_active) {
+            const hipEvent_t* ev = c->tev[j & 1];
+            for (int q = 0; q < (lc.pc ? 5 : 2); ++q) {
+                float t = 0.f;
+                HIPCHK(hipEventElapsedTime(&t, ev[2 * q], ev[2 * q + 1]));
+                const int slot = q < 2 ? kt_a + q : (mixed ? 4 : 7) + q - 2;
+                c->kt.ms[slot] += t;
+                c->kt.count[slot] += 1;
+            }
+            if (size[j & 1] / 2 + 1 < size[j & 1]) {
+                float t = 0.f;
+                HIPCHK(hipEventElapsedTime(&t, ev[10], ev[11]));
+                c->kt.ms[mixed ? 10 : 11] += t;
+                c->kt.count[mixed ? 10 : 11] += 1;
+            }
+        }
+        start_active_prev = all_active;
+        return HMC_OK;
+    };
+    // Chunks are issued one ahead of the status read, so the GPU never idles on the host, except
+    // when the records (or, before the first ones, the last solve) say that the chunk in flight
+    // should be the last: a chunk past the end is some hundred launches that do nothing, 2-5 us each,
+    // where waiting costs 30 us if the estimate was wrong.  In FP64 a chunk's length is free
+    // (nothing but the status check happens at its end): the last one is cut to the estimate.
     for (; !done_early;) {
+        int len = chunk;
+        if (!mixed && !use_graphs && left > 0) len = std::max(8, std::min(chunk, left + 4));
         if (use_graphs) {
             HIPCHK(hipGraphLaunch(c->cgg[mixed ? 1 : 0].exec[k == 0 ? 0 : 1], s));
-            c->seq += nlaunch;
+            c->seq += chunk_launches(chunk, lc.pc);
         } else {
-            int rc = enqueue_chunk<R, Geo>(c, lc, n, phi64, b, x, chunk, ru_filter, k == 0, sample, k & 1, s);
+            int rc = enqueue_chunk<R, Geo>(c, lc, n, phi64, b, x, len, ru_filter, k == 0, sample, k & 1, s);
             if (rc) return rc;
         }
-        issued += chunk;
+        size[k & 1] = len;
+        issued += len;
         HIPCHK(hipMemcpyAsync(c->h_st + size_t(k & 1) * c->nunits, current_states(c), st_bytes,
                               hipMemcpyDeviceToHost, s));
         HIPCHK(hipEventRecord(c->ev[k & 1], s));
         if (have_prev) {
-            HIPCHK(hipEventSynchronize(c->ev[(k - 1) & 1]));
-            const CgState* hs = c->h_st + size_t((k - 1) & 1) * c->nunits;
-            bool all = true, all_active = true;
-            for (int j = 0; j < n; ++j) {
-                all = all && finished(hs[j].mode);
-                all_active = all_active && hs[j].mode == CG_ACTIVE;
-            }
-            // chunk k-1 began in the state chunk k-2 ended in; if every unit was iterating
-            // then and is still iterating at its end, its mid-chunk sample did full work
-            if (sample && start_active_prev && all_active) {
-                const hipEvent_t* ev = c->tev[(k - 1) & 1];
-                for (int q = 0; q < (lc.pc ? 5 : 2); ++q) {
-                    float t = 0.f;
-                    HIPCHK(hipEventElapsedTime(&t, ev[2 * q], ev[2 * q + 1]));
-                    const int slot = q < 2 ? kt_a + q : (mixed ? 4 : 7) + q - 2;
-                    c->kt.ms[slot] += t;
-                    c->kt.count[slot] += 1;
-                }
-                if (chunk / 2 + 1 < chunk) {
-                    float t = 0.f;
-                    HIPCHK(hipEventElapsedTime(&t, ev[10], ev[11]));
-                    c->kt.ms[mixed ? 10 : 11] += t;
-                    c->kt.count[mixed ? 10 : 11] += 1;
-                }
-            }
-            start_active_prev = all_active;
+            int rc = settle(k - 1);
+            if (rc) return rc;
             if (all) break;
+            left -= len;
+        } else if (k == k0) {
+            left = k == 0 && c->sg_last_iters > 0 ? c->sg_last_iters - len : 1;
         }
         have_prev = true;
+        if (left <= 0) {   // expected to end in this chunk
+            int rc = settle(k);
+            if (rc) return rc;
+            have_prev = false;
+            if (all) break;
+        }
         ++k;
         // the device enforces cg_maxit; this bound only guards the host loop
         if (issued > c->p.cg_maxit + 4 * chunk) break;
     }
     if (!done_early) {
-        HIPCHK(hipMemcpyAsync(c->h_st, current_states(c), st_bytes, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        if (all) {
+            // finished records do not change; a chunk issued past them only has to drain
+            if (have_prev) HIPCHK(hipStreamSynchronize(s));
+            if (last != c->h_st) std::memcpy(c->h_st, last, st_bytes);
+        } else {
+            HIPCHK(hipMemcpyAsync(c->h_st, current_states(c), st_bytes, hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+        }
     }
     int status = HMC_OK;
     c->sg_last_iters = 0;
