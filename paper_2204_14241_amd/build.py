@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhmc.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("hmc.hip", "fft_f32.hip", "fft_f64.hip", "fft_metric.hip")]
 DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("kernels.h", "lattice.h", "fft.h", "fft_kernels.h", "precond.h", "metric.h",
-                                                  "probe.h", "march.h")] + [
+                                                  "probe.h", "march.h", "small.h")] + [
     os.path.join(ROOT, "include", f) for f in ("hmc.h", "hmc_testing.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -36,6 +36,7 @@
 #include "lattice.h"
 #include "probe.h"
 #include "march.h"
+#include "small.h"
 
 // Hash of the sources the library was built from (set by the build; keys the tuning cache).
 #ifndef HMC_SOURCE_HASH
@@ -237,6 +238,7 @@ struct hmc_ctx {
     // not yet estimated, per [two-site hops][precision][right-hand sides]); a batch, batch_slices
     bool cgm_auto[2] = {true, true};
     mutable Cut acut[2][2][HMC_MAX_RHS + 1] = {};
+    bool shape_set = false;      // the caller chose a launch shape: no one-kernel solves (small_lattice)
     int cgb_march[2] = {1, 1};   // step B marches too (with step A's cut) [FP64, FP32]
     // partial sums the last launched kernel left per unit when its workgroup count is not the
     // CG launch shape's (a march); the next launch's control block takes it over
@@ -1305,6 +1307,45 @@ static int prepare_graphs(hmc_ctx* c, const Launch<Geo>& lc, int n, const double
     return HMC_OK;
 }
 
+// The status of a solve from the final records in c->h_st.
+static int solve_status(hmc_ctx* c, int n) {
+    int status = HMC_OK;
+    c->sg_last_iters = 0;
+    for (int j = 0; j < n; ++j) c->sg_last_iters = std::max(c->sg_last_iters, c->h_st[j].iters);
+    for (int j = 0; j < n; ++j) {
+        const CgState& h = c->h_st[j];
+        if (h.mode == CG_FAILED) status = HMC_ERR_NONFINITE;
+        else if (h.mode != CG_DONE && status == HMC_OK) status = HMC_ERR_NOT_CONVERGED;
+    }
+    if (status == HMC_ERR_NONFINITE) return fail(status, "CG met a non-finite value");
+    if (status == HMC_ERR_NOT_CONVERGED)
+        return fail(status, "CG did not reach tol %.3g within %d iterations", c->p.cg_tol, c->p.cg_maxit);
+    return HMC_OK;
+}
+
+// Whether a solve runs as one kernel (small.h): FP64 without preconditioner on at most kSmallSites
+// sites.  us per iteration, chunked -> one kernel: 4 x 4 x 8 10.3 -> 2.0, 4 x 4 x 32 10.5 -> 3.0, 8 x 8 x 8
+// with 16 right-hand sides 10.8 -> 3.0, 6 x 6 x 14 with the two-site hops 10.8 -> 4.4.  Beyond 512 sites a
+// 1024-thread workgroup has 128 registers a thread and spills: 6 x 6 x 16 10.6 -> 8.0, 8 x 8 x 16 10.5 -> 11.4, with
+// the two-site hops 10.9 -> 17.9.  Not while the caller has set a launch shape of the CG kernels or
+// samples their times.
+static bool small_lattice(const hmc_ctx* c, bool pc) {
+    return !c->is_batch && !pc && c->vol <= kSmallSites && !c->shape_set && !c->timing;
+}
+
+static int small_solve(hmc_ctx* c, bool nn2, int n, const double* phi, const double2* b, double2* x, hipStream_t s) {
+    const int threads = (c->vol + 63) / 64 * 64;
+    const double tol2 = c->p.cg_tol * c->p.cg_tol;
+    c->seq = 0;
+    c->next_nparts = 0;
+    HMC_LAUNCH_NN2(nn2, (k_cg_small<true>), (k_cg_small<false>), dim3(n), dim3(threads), small_lds(c->vol), s, c->lat, b,
+                   x, phi, c->cf64, c->st, tol2, c->p.cg_maxit);
+    LAUNCHCHK();
+    HIPCHK(hipMemcpyAsync(c->h_st, c->st, sizeof(CgState) * size_t(n), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    return solve_status(c, n);
+}
+
 // Solve (M^dagger M) x_u = b_u for the n units of the launch.  Final records are left in
 // c->h_st[0 .. n).  Returns HMC_OK, HMC_ERR_NOT_CONVERGED or HMC_ERR_NONFINITE.
 // The start of a solve: FP32 copy of phi (mixed precision), the CG start (x = 0, r = b, |b|^2),
@@ -1339,7 +1380,6 @@ template <typename R, class Geo>
 static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64, const double2* b,
                   double2* x, hipStream_t s, int k0 = 0) {
     const bool mixed = sizeof(R) == sizeof(float);
-    const double tol = c->p.cg_tol;
     const int chunk = mixed ? c->p.reliable_every : kCheckEvery;
     const int ru_filter = mixed ? (F_ACTIVE | F_CONV_ITER | F_MAXIT) : (F_CONV_ITER | F_MAXIT);
     const bool use_graphs = c->graphs;
@@ -1453,18 +1493,7 @@ static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64,
             HIPCHK(hipStreamSynchronize(s));
         }
     }
-    int status = HMC_OK;
-    c->sg_last_iters = 0;
-    for (int j = 0; j < n; ++j) c->sg_last_iters = std::max(c->sg_last_iters, c->h_st[j].iters);
-    for (int j = 0; j < n; ++j) {
-        const CgState& h = c->h_st[j];
-        if (h.mode == CG_FAILED) status = HMC_ERR_NONFINITE;
-        else if (h.mode != CG_DONE && status == HMC_OK) status = HMC_ERR_NOT_CONVERGED;
-    }
-    if (status == HMC_ERR_NONFINITE) return fail(status, "CG met a non-finite value");
-    if (status == HMC_ERR_NOT_CONVERGED)
-        return fail(status, "CG did not reach tol %.3g within %d iterations", tol, c->p.cg_maxit);
-    return HMC_OK;
+    return solve_status(c, n);
 }
 
 // A leapfrog step's drift (drift_pi non-null: phi += eps pi) and solve, or a trajectory's first
@@ -1546,6 +1575,15 @@ static int drift(hmc_ctx* c, double* phi, const double* pi, double eps, hipStrea
 template <typename R, class Geo>
 static int drift_solve(hmc_ctx* c, const Launch<Geo>& lc, int n, double* phi, const double* pi, double eps,
                        const double2* b, double2* x, hipStream_t s) {
+    if constexpr (std::is_same<Geo, GeoOne>::value && sizeof(R) == sizeof(double)) {
+        if (small_lattice(c, lc.pc)) {
+            if (pi) {
+                int rc = drift(c, phi, pi, eps, s);
+                if (rc) return rc;
+            }
+            return small_solve(c, lc.nn2, n, phi, b, x, s);
+        }
+    }
     if (c->step_graphs && c->sigma == nullptr && c->sg_last_iters > 0)
         return solve_step_graph<R, Geo>(c, lc, n, phi, pi, eps, b, x, s);
     if (pi) {
@@ -2073,6 +2111,8 @@ static int autotune_common(hmc_ctx* c, const double* phi, const double2* b, int 
                            hipStream_t s) {
     static const int cand[HMC_TUNE_MAX] = {128, 256, 384, 512, 640, 768, 1024, 1280, 1536, 2048, 3072, 4096};
     const hmc_params saved = c->p;
+    const bool saved_set = c->shape_set;
+    c->shape_set = true;                // the kernels whose shapes are timed
     const int iters = 100;
     std::memset(out, 0, sizeof(*out));
     hipEvent_t e0, e1;
@@ -2213,6 +2253,7 @@ static int autotune_common(hmc_ctx* c, const double* phi, const double2* b, int 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     c->p = saved;
+    c->shape_set = saved_set;
     if (result != HMC_OK) {
         for (int pi = 0; pi < 2; ++pi) {
             c->cgm_rows[pi] = kDefaultRows[pi];
@@ -2814,6 +2855,7 @@ int hmc_set_cg_workgroups(hmc_ctx* c, int precision, int max_per_rhs) {
         return fail(HMC_ERR_INVALID_ARG, "precision must be HMC_FP64, HMC_MIXED or -1");
     if (max_per_rhs < 1 || max_per_rhs > kMaxBpr)
         return fail(HMC_ERR_INVALID_ARG, "workgroups per right-hand side must lie in [1, %d]", kMaxBpr);
+    c->shape_set = true;
     return set_cg_shape(c, precision, max_per_rhs);
 }
 
@@ -2838,6 +2880,7 @@ int hmc_set_cg_march(hmc_ctx* c, int precision, int rows, int slices) {
         return fail(HMC_ERR_INVALID_ARG, "unknown precision");
     if (rows < 0 || rows > 256 || slices < 0 || slices > 1 << 20)
         return fail(HMC_ERR_INVALID_ARG, "rows must lie in [0, 256] and slices be >= 0");
+    c->shape_set = true;
     for (int pi = 0; pi < 2; ++pi)
         if (precision == -1 || precision == (pi ? HMC_MIXED : HMC_FP64)) {
             c->cgm_rows[pi] = rows;
@@ -2854,6 +2897,7 @@ int hmc_set_cg_march_step_b(hmc_ctx* c, int precision, int enable) {
         return fail(HMC_ERR_INVALID_ARG, "unknown precision");
     for (int pi = 0; pi < 2; ++pi)
         if (precision == -1 || precision == (pi ? HMC_MIXED : HMC_FP64)) c->cgb_march[pi] = enable != 0;
+    c->shape_set = true;
     c->generation += 1;   // captured graphs hold the launch shape
     return HMC_OK;
 }
