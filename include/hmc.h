@@ -379,8 +379,8 @@ int hmc_get_cg_workgroups(const hmc_ctx* ctx, int precision);
  * nearest-neighbour operator): each workgroup owns a band of `rows` lattice rows of one vector
  * and marches through `slices` consecutive time slices, holding M in for its rows and the rows
  * beside them in LDS; with slices = 1 each workgroup takes one slice of its band and forms
- * M in at the previous slice itself.  0 selects the default (12 rows FP32, 6 rows FP64, one
- * slice; rows are capped so that the band's M in fits 64 KB of LDS).  precision: HMC_FP64,
+ * M in at the previous slice itself.  0 selects the default (8 rows FP32, 4 rows FP64, 8 slices;
+ * with both 0, the shape with the least estimated time for the lattice and the vectors).  precision: HMC_FP64,
  * HMC_MIXED or -1 for both.  Results do not depend on the shape.  hmc_get_mdm_shape reports the
  * shape an apply of n vectors uses: rows, slices and the workgroup count (host ints). */
 int hmc_set_mdm_shape(hmc_ctx* ctx, int precision, int rows, int slices);

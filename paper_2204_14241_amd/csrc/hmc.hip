@@ -230,6 +230,7 @@ struct hmc_ctx {
     // default for the lattice
     int mdm_rows[2] = {0, 0};
     int mdm_seg[2] = {0, 0};
+    mutable Cut amdm[2][HMC_MAX_RHS + 1] = {};   // auto_mdm's choice per number of vectors (rows 0: not yet made)
     // CG step A as a march (march.h) [FP64, FP32]: rows per band (0: the tile kernels) and slices
     // per segment (0: the default)
     int cgm_rows[2] = {0, 0};
@@ -2307,10 +2308,49 @@ static int apply_impl(hmc_ctx* c, const R* phi, const void* in, void* out, int n
     return launch_apply<R, DAG>(c, phi, in, out, n, (hipStream_t)stream);
 }
 
+// The march cut of the one-pass M^dagger M of n vectors when none was set, chosen like auto_cut's
+// from an estimate fitted to 1,100 shapes of 19 lattices (4 x 4 x 8 to 80 x 80 x 200, 1 to 4 vectors), where it takes
+// 1.03x (FP32) and 1.01x (FP64) the best shape's time: the dependent steps of a round of
+// workgroups (a segment forms three slices before its first result), the traffic, and the busiest
+// CU's.  us, with 8 (FP32) or 4 (FP64) rows and 8 slices -> chosen: 12 x 12 x 40 FP64 12.9 -> 7.4 (what the call costs),
+// 40 x 40 x 100 FP64 16.2 -> 9.8, 60 x 60 x 160 FP64 37.2 -> 23.3, 80 x 80 x 40 FP32 19.8 -> 9.4, 80 x 80 x 200 FP32 two
+// vectors 50.0 -> 44.6; 80 x 80 x 200 with one vector keeps its cut (24.7 FP32, 50.5 FP64).
+static Cut auto_mdm(int L, int Lt, int n, int pi) {
+    static const double coef[2][4] = {{2.06, 0.795, 0.0008, 0.0531}, {0.74, 1.19, 0.0019, 0.0426}};
+    static const int segs[] = {2, 3, 4, 6, 8, 12};
+    const double* k = coef[pi];
+    const int per_row = pi ? L / 2 : L;
+    auto threads = [&](int R) { return ((std::min(R, L) + 4) * per_row + 63) / 64 * 64; };
+    auto lds = [&](int R) { return pi ? mdm_march_lds<float>(std::min(R, L), L) : mdm_march_lds<double>(std::min(R, L), L); };
+    auto estimate = [&](int R, int s) {
+        const MarchPlan mp = make_march_plan(L, Lt, R, s);
+        const long long wgs = (long long)mp.nband * mp.nseg * n;
+        const int waves = threads(R) / 64, by_waves = (waves <= 8 ? 16 : 12) / waves;
+        const int resident = std::max(1, std::min(by_waves, int((size_t(160) << 10) / lds(R))));
+        const long long busy = (wgs + 255) / 256, rounds = (busy + resident - 1) / resident;
+        const double sl = mp.seglen;
+        const double reals = 8.0 * (mp.R + 4) / mp.R * (sl + 3) / sl + 3.0 * (mp.R + 2) / mp.R * (sl + 1) / sl + 8.0;
+        const double mb = reals * (pi ? 4 : 8) * 1e-6;
+        return k[0] + k[1] * double(rounds) * (sl + 3) + k[2] * mb * L * L * Lt * n +
+               k[3] * mb * 256.0 * double(busy) * sl * mp.R * L;
+    };
+    Cut best{kDefaultRows[pi], kDefaultSlices};
+    double least = 0.95 * estimate(best.rows, best.slices);
+    for (int R = 1; R <= L && threads(R) <= kMdmMidThreads && lds(R) <= (size_t(160) << 10); ++R)
+        for (int s : segs) {
+            if (s > Lt) break;
+            const double t = estimate(R, s);
+            if (t < least) {
+                least = t;
+                best = Cut{R, s};
+            }
+        }
+    return best;
+}
+
 // Launch shape of the fused M^dagger M for n vectors: rows per band, slices per segment (1: one
 // workgroup per slice and band, k_mdm*_tile, whose chi rows fit 64 KB of LDS; more: the march,
-// k_mdm*_march), threads (one per element of the rows a workgroup holds, at most 512).  The
-// shape does not depend on n.
+// k_mdm*_march), threads (one per element of the rows a workgroup holds, at most 512).
 struct MdmShape {
     MarchPlan plan;
     int threads;
@@ -2321,12 +2361,20 @@ template <typename R>
 static MdmShape mdm_shape(const hmc_ctx* c, int n) {
     const int pi = sizeof(R) == sizeof(float) ? 1 : 0;
     const int L = c->L, Lt = c->Lt, per_row = pi ? L / 2 : L;
-    // defaults: the fastest shapes at 80 x 80 x 200 (the march: 8 rows FP32, 4 rows FP64, 8 slices)
-    int rows = c->mdm_rows[pi] > 0 ? c->mdm_rows[pi] : (pi ? 8 : 4);
+    Cut cut{c->mdm_rows[pi] > 0 ? c->mdm_rows[pi] : kDefaultRows[pi], c->mdm_seg[pi] > 0 ? c->mdm_seg[pi] : kDefaultSlices};
+    if (c->mdm_rows[pi] <= 0 && c->mdm_seg[pi] <= 0) {
+        if (n <= HMC_MAX_RHS) {
+            Cut& kept = c->amdm[pi][n];
+            if (kept.rows == 0) kept = auto_mdm(L, Lt, n, pi);
+            cut = kept;
+        } else {
+            cut = auto_mdm(L, Lt, n, pi);
+        }
+    }
+    int rows = cut.rows;
     const int rows_lds = int((size_t(64) << 10) / (4 * size_t(L) * sizeof(C2<R>))) - 2;
     rows = std::max(1, std::min({rows, rows_lds, 4 * kMarchMaxThreads / per_row}));
-    const int seg = c->mdm_seg[pi] > 0 ? c->mdm_seg[pi] : 8;
-    (void)n;
+    const int seg = cut.slices;
     MdmShape m;
     m.tile = seg == 1;
     if (m.tile) {

@@ -47,3 +47,22 @@ def test_small_batch_cut(hip):
     assert [bt.cg_march(i, "mixed")[0] for i in range(2)] == [(8, 1), (8, 1)]
     bt.set_cg_march(8, 8)
     assert [bt.cg_march(i, "mixed")[0] for i in range(2)] == [(8, 8), (8, 8)]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("L,Lt,n", [(4, 2, 1), (6, 3, 3), (14, 11, 2), (34, 9, 1), (60, 13, 1), (128, 2, 1)])
+def test_default_one_pass_shape(hip, precision, L, Lt, n):
+    """M^dagger M at the shape chosen by itself (Eq. 22) against the oracle: 1e-14 (FP64) and 2e-6 (FP32, on
+    the rounded inputs) of the largest entry, the bars of the one-pass kernels at set shapes."""
+    import torch
+    m = O.Model(L=L, Lt=Lt)
+    g = S.rng(5 * L + Lt)
+    phi, psi = S.draw_phi(g, L, Lt, 0.5), S.draw_spinor(g, L, Lt, n)
+    h = hip.HMC(L, Lt, max_rhs=n)
+    print(f"one pass {precision} {L}x{L}x{Lt} n={n} shape {h.mdm_shape(precision, n)}", flush=True)
+    if precision == "mixed":
+        phi, psi = phi.astype(np.float32), psi.astype(np.complex64)
+    f = h.apply_MdagM_f32 if precision == "mixed" else h.apply_MdagM
+    got = f(torch.from_numpy(phi).cuda(), torch.from_numpy(psi).cuda()).cpu().numpy().astype(np.complex128)
+    want = np.stack([O.apply_MdagM(m, phi.astype(np.float64), psi[k].astype(np.complex128)) for k in range(n)])
+    assert np.abs(got.reshape(want.shape) - want).max() <= (2e-6 if precision == "mixed" else 1e-14) * np.abs(want).max()
