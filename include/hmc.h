@@ -396,8 +396,9 @@ int hmc_get_mdm_shape(const hmc_ctx* ctx, int precision, int n, int* rows, int* 
  * contexts: a cut estimated per launch from the lattice and the right-hand sides (8 rows FP32 / 4
  * rows FP64 and 8 slices where the lattice fills the chip, fewer slices or other bands on smaller
  * ones), or the autotuner's choice.  FP64 solves without preconditioner on at most 512 sites run as
- * one kernel instead, until a launch shape is set here, with hmc_set_cg_march_step_b or with
- * hmc_set_cg_workgroups, and while kernel times are sampled.  precision:
+ * one kernel instead, and preconditioned solves on small lattices run steps A and B joined with the
+ * preconditioner's slice passes (three launches an iteration), until a launch shape is set here, with
+ * hmc_set_cg_march_step_b or with hmc_set_cg_workgroups, and while kernel times are sampled.  precision:
  * HMC_FP64, HMC_MIXED or -1 for both.  The algebra is that of the tile kernels; only the order
  * of the FP64 partial sums differs.  One-lattice contexts only (HMC_ERR_INVALID_ARG on a
  * batch: hmc_batch_set_cg_march); lattices whose band does not fit (rows + 2 rows, or rows + 4

@@ -406,29 +406,47 @@ __host__ __device__ __forceinline__ void fft_slice_pos(const FftPlan& pl, int i,
     px = it - b * pl.n;
     py = b * sg.radix + q;
 }
+// The two ways' middle, for callers that have or want the slices in the working copy: forward from
+// the working copy, its stages along x from sx on, to dst(slice, element); the inverse from
+// src(slice, element), its stages along x down to sx, into the working copy (synchronised).
+template <typename R, int MAXR = kFftMaxRadix, class Ex, class Dst>
+__host__ __device__ __forceinline__ void fft_slices_out(const Ex& ex, C2<R>* buf, const Dst& dst, int ns, int P,
+                                                        const FftPlan& pl, const C2<R>* tw, int sx) {
+    const int L = pl.n, nst = pl.nst;
+    const Lines col{L, P, 1, L * P, ns, pl.dn}, row{L, 1, P, L * P, ns, pl.dn};
+    const int per_out = int(pl.dout.d);      // items of a slice in the last stage along y
+    fft_lines<R, false, MAXR>(ex, buf, col, pl, tw, sx, nst);
+    fft_lines<R, false, MAXR>(ex, buf, row, pl, tw, 0, nst - 1);
+    fft_one_stage<R, false, MAXR>(
+        ex, pl, nst - 1, row, tw, [&](int set, int, int c, int, int pos) HMC_FLAT { return buf[set * row.sp + c * P + pos]; },
+        [&](int set, int it, int, int q, int, C2<R> v) HMC_FLAT { dst(set, q * per_out + it, v); });
+}
+template <typename R, int MAXR = kFftMaxRadix, class Ex, class Src>
+__host__ __device__ __forceinline__ void fft_slices_in(const Ex& ex, const Src& src, C2<R>* buf, int ns, int P,
+                                                       const FftPlan& pl, const C2<R>* tw, int sx) {
+    const int L = pl.n, nst = pl.nst;
+    const Lines col{L, P, 1, L * P, ns, pl.dn}, row{L, 1, P, L * P, ns, pl.dn};
+    const int per_out = int(pl.dout.d);
+    fft_one_stage<R, true, MAXR>(
+        ex, pl, nst - 1, row, tw, [&](int set, int it, int, int q, int) HMC_FLAT { return src(set, q * per_out + it); },
+        [&](int set, int, int c, int, int pos, C2<R> v) HMC_FLAT { buf[set * row.sp + c * P + pos] = v; });
+    ex.sync();
+    fft_lines<R, true, MAXR>(ex, buf, row, pl, tw, 0, nst - 1);
+    fft_lines<R, true, MAXR>(ex, buf, col, pl, tw, sx, nst);
+}
 template <typename R, bool INV, int MAXR = kFftMaxRadix, class Ex, class Src, class Dst>
 __host__ __device__ __forceinline__ void fft_slices(const Ex& ex, const Src& src, C2<R>* buf, const Dst& dst, int ns,
                                                     int P, const FftPlan& pl, const C2<R>* tw) {
-    const int L = pl.n, LL = L * L, nst = pl.nst;
-    const Lines col{L, P, 1, L * P, ns, pl.dn}, row{L, 1, P, L * P, ns, pl.dn};
-    const int per_out = int(pl.dout.d);      // items of a slice in the last stage along y
+    const int L = pl.n, LL = L * L;
+    const Lines col{L, P, 1, L * P, ns, pl.dn};
     if constexpr (!INV) {
         fft_one_stage<R, false, MAXR>(
             ex, pl, 0, col, tw, [&](int set, int, int c, int, int pos) HMC_FLAT { return src(set * LL + pos * L + c); },
             [&](int set, int, int c, int, int pos, C2<R> v) HMC_FLAT { buf[set * col.sp + c + pos * P] = v; });
         ex.sync();
-        fft_lines<R, false, MAXR>(ex, buf, col, pl, tw, 1, nst);
-        fft_lines<R, false, MAXR>(ex, buf, row, pl, tw, 0, nst - 1);
-        fft_one_stage<R, false, MAXR>(
-            ex, pl, nst - 1, row, tw, [&](int set, int, int c, int, int pos) HMC_FLAT { return buf[set * row.sp + c * P + pos]; },
-            [&](int set, int it, int, int q, int, C2<R> v) HMC_FLAT { dst(set * LL + q * per_out + it, v); });
+        fft_slices_out<R, MAXR>(ex, buf, [&](int set, int i, C2<R> v) HMC_FLAT { dst(set * LL + i, v); }, ns, P, pl, tw, 1);
     } else {
-        fft_one_stage<R, true, MAXR>(
-            ex, pl, nst - 1, row, tw, [&](int set, int it, int, int q, int) HMC_FLAT { return src(set * LL + q * per_out + it); },
-            [&](int set, int, int c, int, int pos, C2<R> v) HMC_FLAT { buf[set * row.sp + c * P + pos] = v; });
-        ex.sync();
-        fft_lines<R, true, MAXR>(ex, buf, row, pl, tw, 0, nst - 1);
-        fft_lines<R, true, MAXR>(ex, buf, col, pl, tw, 1, nst);
+        fft_slices_in<R, MAXR>(ex, [&](int set, int i) HMC_FLAT { return src(set * LL + i); }, buf, ns, P, pl, tw, 1);
         fft_one_stage<R, true, MAXR>(
             ex, pl, 0, col, tw, [&](int set, int, int c, int, int pos) HMC_FLAT { return buf[set * col.sp + c + pos * P]; },
             [&](int set, int, int c, int, int pos, C2<R> v) HMC_FLAT { dst(set * LL + pos * L + c, v); });

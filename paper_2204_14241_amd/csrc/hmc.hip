@@ -239,7 +239,8 @@ struct hmc_ctx {
     // not yet estimated, per [two-site hops][precision][right-hand sides]); a batch, batch_slices
     bool cgm_auto[2] = {true, true};
     mutable Cut acut[2][2][HMC_MAX_RHS + 1] = {};
-    bool shape_set = false;      // the caller chose a launch shape: no one-kernel solves (small_lattice)
+    bool shape_set = false;      // the caller chose a launch shape: no one-kernel solves (small_lattice), no
+                                 // joined steps (join_step)
     int cgb_march[2] = {1, 1};   // step B marches too (with step A's cut) [FP64, FP32]
     // partial sums the last launched kernel left per unit when its workgroup count is not the
     // CG launch shape's (a march); the next launch's control block takes it over
@@ -793,6 +794,12 @@ struct Launch {
     MarchPlan rum{};
     int rum_threads = 0, rum_per_unit = 0;
     size_t rum_lds = 0;
+    // steps A and B joined with the slice passes (one lattice): geometry, threads and LDS
+    bool join_a = false, join_b = false;
+    GeoOne ps{};
+    int joined() const { return (join_a ? 1 : 0) + (join_b ? 2 : 0); }
+    int ps_threads = 0;
+    size_t ps_lds[2] = {};   // [step A, step B]
     // a batch's marches: every unit with its own cut (0 workgroups: the tile kernels)
     MGeoBatch bm{}, br{};
     int bm_grid = 0, bm_threads = 0, br_grid = 0, br_threads = 0;
@@ -854,6 +861,27 @@ static Cut cut_of(const hmc_ctx* c, int pi, int n) {
     return kept;
 }
 
+// Whether a preconditioned solve joins step A (step_b false) or B with the slice pass beside it
+// (pcstep.h), one workgroup per slice of a vector, from 250 lattices, vector counts and precisions
+// of 4 x 4 x 8 to 48 x 48 x 120 (us per iteration, apart -> B joined -> both joined).
+// Either step: as long as two workgroups fit a CU's LDS, or all of them run at once: FP32 16 x 16 x 80 with
+// four vectors 33.6 -> 31.4 -> 26.3, 28 x 28 x 150 with four 75.7 -> 67.8 -> 58.3; but FP32 40 x 40 x 160 with two, one
+// workgroup a CU and a quarter of a second round of them, 74.3 -> 76.7 -> 82.7.
+// Step A transforms two slices for one, which has to be little (FP32 L <= 24, FP64 L <= 16: 24 x 24 x 40 with one
+// vector 28.6 -> 30.0 -> 27.7) or done on CUs that are busy anyway: FP64 28 x 28 x 40 with two vectors 38.3 -> 36.9 ->
+// 41.3, 24 x 24 x 40 with four 40.7 -> 38.5 -> 37.6.
+// Not while the caller has set a launch shape of the CG kernels or samples their times.
+constexpr size_t kJoinSlice = 24 * 24 * sizeof(float2);
+constexpr int kJoinWgs = 160;
+template <typename R>
+static bool join_step(const hmc_ctx* c, int n, bool step_b) {
+    const size_t lds = pc_step_lds<R>(c->L, c->L + 1, step_b);
+    const int wgs = c->Lt * n;
+    if (c->shape_set || c->timing || lds > kPcLdsMost || c->Lt > c->pstride) return false;
+    if (2 * lds > kPcLdsMost && wgs > 256) return false;
+    return step_b || c->lat.LL * sizeof(C2<R>) <= kJoinSlice || wgs >= kJoinWgs;
+}
+
 template <typename R>
 static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
     const int pi = sizeof(R) == sizeof(float) ? 1 : 0;
@@ -895,6 +923,13 @@ static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
             l.cgm_threads = ((std::min(rows, c->L) + 2 * H) * per_row + 63) / 64 * 64;
             l.cgm_lds = lds;
         }
+    }
+    if (l.pc && l.cgm_per_unit > 0 && l.cgbm) {
+        l.join_a = join_step<R>(c, n, false);
+        l.join_b = join_step<R>(c, n, true);
+        l.ps = GeoOne{c->lat, c->Lt, c->Lt, c->pstride, SliceCut{1, c->L + 1}};
+        l.ps_threads = std::min(kPcBlock, (c->lat.LL + 63) / 64 * 64);
+        for (int b = 0; b < 2; ++b) l.ps_lds[b] = pc_step_lds<R>(c->L, c->L + 1, b != 0);
     }
     // the reliable update's FP64 marches: one thread per element of the band and its two
     // neighbour rows, as the FP64 step-A march
@@ -1015,41 +1050,72 @@ static void launch_timed(void (*k)(P...), int grid, int block, size_t lds, hipSt
     else hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, s, static_cast<P>(a)...);
 }
 
-// The three preconditioner passes, z = P r, for the units whose residual just changed; the
-// first consumes the pending kind `expect1` (a new |r|^2, the first |b|^2 or a true residual).
+// The preconditioner passes, z = P r, for the units whose residual just changed; the first consumes
+// the pending kind `expect1` (a new |r|^2, the first |b|^2 or a true residual).  first, last: the
+// passes to run (0 forward, 1 tau, 2 inverse).
 template <typename R, class Geo, int MAXR>
 static int enqueue_pc_r(hmc_ctx* c, const Launch<Geo>& lc, const CgVecs<R>& v, int expect1, hipStream_t s,
-                        hipEvent_t* e) {
+                        hipEvent_t* e, int first, int last) {
     // e: null, or the start/stop events of the three passes (timed by their own dispatches)
-    launch_timed(k_pc_xy<R, false, Geo, MAXR>, lc.npxy, lc.xy_threads, lc.lds_xy, s, e, 0,
-                 next_ctl(c, expect1), lc.pxy, v.r, v.z, c->blob);
-    LAUNCHCHK();
-    if (lc.pt_full)
-        launch_timed(k_pc_t<R, Geo, true>, lc.npt, lc.pt_threads, lc.lds_t, s, e, 1,
-                     next_ctl(c, PEND_NONE), lc.pt, v.z, c->blob, c->cf64);
-    else
-        launch_timed(k_pc_t<R, Geo, false>, lc.npt, lc.pt_threads, lc.lds_t, s, e, 1,
-                     next_ctl(c, PEND_NONE), lc.pt, v.z, c->blob, c->cf64);
-    LAUNCHCHK();
-    launch_timed(k_pc_xy<R, true, Geo, MAXR>, lc.npxy, lc.xy_threads, lc.lds_xy, s, e, 2,
-                 next_ctl(c, PEND_RZ), lc.pxy, v.z, v.z, c->blob);
-    LAUNCHCHK();
+    if (first <= 0) {
+        launch_timed(k_pc_xy<R, false, Geo, MAXR>, lc.npxy, lc.xy_threads, lc.lds_xy, s, e, 0,
+                     next_ctl(c, expect1), lc.pxy, v.r, v.z, c->blob);
+        LAUNCHCHK();
+    }
+    if (first <= 1 && last >= 1) {
+        const CgCtl kt = next_ctl(c, first == 1 ? expect1 : PEND_NONE);
+        if (lc.pt_full)
+            launch_timed(k_pc_t<R, Geo, true>, lc.npt, lc.pt_threads, lc.lds_t, s, e, 1, kt, lc.pt, v.z, c->blob, c->cf64);
+        else
+            launch_timed(k_pc_t<R, Geo, false>, lc.npt, lc.pt_threads, lc.lds_t, s, e, 1, kt, lc.pt, v.z, c->blob, c->cf64);
+        LAUNCHCHK();
+    }
+    if (last >= 2) {
+        launch_timed(k_pc_xy<R, true, Geo, MAXR>, lc.npxy, lc.xy_threads, lc.lds_xy, s, e, 2,
+                     next_ctl(c, PEND_RZ), lc.pxy, v.z, v.z, c->blob);
+        LAUNCHCHK();
+    }
     return HMC_OK;
 }
 
 template <typename R, class Geo>
 static int enqueue_pc(hmc_ctx* c, const Launch<Geo>& lc, const CgVecs<R>& v, int expect1, hipStream_t s,
-                      hipEvent_t* e = nullptr) {
-    return lc.wide ? enqueue_pc_r<R, Geo, kFftMaxRadix>(c, lc, v, expect1, s, e)
-                   : enqueue_pc_r<R, Geo, kFftNarrow>(c, lc, v, expect1, s, e);
+                      hipEvent_t* e = nullptr, int first = 0, int last = 2) {
+    return lc.wide ? enqueue_pc_r<R, Geo, kFftMaxRadix>(c, lc, v, expect1, s, e, first, last)
+                   : enqueue_pc_r<R, Geo, kFftNarrow>(c, lc, v, expect1, s, e, first, last);
+}
+
+// Step A (step_b false) or B joined with the slice passes beside it.
+template <typename R>
+static int enqueue_joined(hmc_ctx* c, const Launch<GeoOne>& lc, bool step_b, int n, const CgCtl& k, const CgVecs<R>& v,
+                          const R* phik, const Coef<R>& cf, hipStream_t s) {
+    auto go = [&](auto nn2, auto maxr) {
+        constexpr bool N2 = decltype(nn2)::value;
+        constexpr int MAXR = decltype(maxr)::value;
+        auto* kern = step_b ? &k_pc_b<R, N2, MAXR> : &k_pc_a<R, N2, MAXR>;
+        hipLaunchKernelGGL(kern, dim3(c->Lt * n), dim3(lc.ps_threads), lc.ps_lds[step_b ? 1 : 0], s, k, lc.ps, v, phik, cf,
+                           c->blob);
+    };
+    auto by_radix = [&](auto nn2) {
+        if (lc.wide) go(nn2, std::integral_constant<int, kFftMaxRadix>{});
+        else go(nn2, std::integral_constant<int, kFftNarrow>{});
+    };
+    if (lc.nn2) by_radix(std::true_type{});
+    else by_radix(std::false_type{});
+    LAUNCHCHK();
+    return HMC_OK;
 }
 
 // Launches of one status chunk (kept even, so that every chunk starts at the same record
-// parity): without preconditioner 2 per iteration + 4; with it 5 per iteration + 6, plus a
-// finalize if odd.
-static int chunk_launches(int chunk, bool pc) {
+// parity): without preconditioner 2 per iteration + 4; with it 5 per iteration + 6, one per iteration
+// less for each step joined with its slice pass (the first step A and the last inverse pass of a
+// chunk stand alone), plus a finalize if odd.
+static int pc_chunk_launches(int chunk, int joined) {
+    return (5 - (joined & 1) - (joined >> 1)) * chunk + 6 + (joined & 1);
+}
+static int chunk_launches(int chunk, bool pc, int joined) {
     if (!pc) return 2 * chunk + 4;
-    const int n = 5 * chunk + 6;
+    const int n = pc_chunk_launches(chunk, joined);
     return n + (n & 1);
 }
 
@@ -1096,7 +1162,40 @@ static int enqueue_chunk(hmc_ctx* c, const Launch<Geo>& lc, int n, const double*
     const Coef<R> cf = KrylovBufs<R>::cf(c);
     const Geo geo = lc.cg;
     const int grid = lc.ncg;
-    for (int i = 0; i < chunk; ++i) {
+    int apart = chunk;    // iterations whose steps and passes are launches of their own
+    if constexpr (std::is_same<Geo, GeoOne>::value) {
+        if (lc.joined()) {
+            apart = 0;
+            for (int i = 0; i < chunk; ++i) {
+                int rc = HMC_OK;
+                // the chunk's first step A finds z already transformed back
+                if (i > 0 && lc.join_a) {
+                    rc = enqueue_joined<R>(c, lc, false, n, next_ctl(c, PEND_RZ), v, phik, cf, s);
+                    if (rc) return rc;
+                    c->next_nparts = c->Lt;
+                } else {
+                    launch_step_march<R, Geo>(c, lc, false, next_ctl(c, PEND_NONE), v, phik, cf, lc.cgm_per_unit * n,
+                                              lc.cgm_threads, lc.cgm_lds, nullptr, s);
+                    LAUNCHCHK();
+                    c->next_nparts = lc.cgm_per_unit;
+                }
+                if (lc.join_b) {
+                    rc = enqueue_joined<R>(c, lc, true, n, next_ctl(c, PEND_TT), v, phik, cf, s);
+                    if (rc) return rc;
+                    c->next_nparts = c->Lt;
+                } else {
+                    launch_step_march<R, Geo>(c, lc, true, next_ctl(c, PEND_TT), v, phik, cf, lc.cgm_per_unit * n,
+                                              lc.cgm_threads, lc.cgm_lds, nullptr, s);
+                    LAUNCHCHK();
+                    c->next_nparts = lc.cgm_per_unit;
+                }
+                rc = enqueue_pc<R, Geo>(c, lc, v, PEND_RR, s, nullptr, lc.join_b ? 1 : 0,
+                                        lc.join_a && i + 1 < chunk ? 1 : 2);
+                if (rc) return rc;
+            }
+        }
+    }
+    for (int i = 0; i < apart; ++i) {
         const int expect_a = lc.pc ? PEND_NONE : (i > 0 ? PEND_RR : (first ? PEND_BB : PEND_NONE));
         const CgCtl ka = next_ctl(c, expect_a);
         // step A as a march (one lattice, or every unit of a batch with its own cut); step B, a
@@ -1251,7 +1350,7 @@ static int enqueue_chunk(hmc_ctx* c, const Launch<Geo>& lc, int n, const double*
     if (lc.pc) {
         int rc = enqueue_pc<R, Geo>(c, lc, v, PEND_RU, s);
         if (rc) return rc;
-        if ((5 * chunk + 6) & 1) {
+        if (pc_chunk_launches(chunk, lc.joined()) & 1) {
             hipLaunchKernelGGL(k_cg_finalize<Geo>, dim3(n), dim3(kBlock), 0, s, next_ctl(c, PEND_NONE), geo, 0);
             LAUNCHCHK();
         }
@@ -1272,7 +1371,7 @@ static int prepare_graphs(hmc_ctx* c, const Launch<Geo>& lc, int n, const double
     CgGraphs& G = c->cgg[pi];
     const auto key = std::make_tuple(lc.ncg, (const void*)phi64, (const void*)b, (const void*)x,
                                      (const void*)c->st, n, chunk, filter, c->nunits, c->generation,
-                                     lc.pc ? 1 : 0);
+                                     (lc.pc ? 1 : 0) + 2 * lc.joined());
     if (G.exec[0] != nullptr && G.key == key) return HMC_OK;
     for (int g = 0; g < 2; ++g) {
         if (G.exec[g]) (void)hipGraphExecDestroy(G.exec[g]);
@@ -1455,7 +1554,7 @@ static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64,
         if (!mixed && !use_graphs && left > 0) len = std::max(8, std::min(chunk, left + 4));
         if (use_graphs) {
             HIPCHK(hipGraphLaunch(c->cgg[mixed ? 1 : 0].exec[k == 0 ? 0 : 1], s));
-            c->seq += chunk_launches(chunk, lc.pc);
+            c->seq += chunk_launches(chunk, lc.pc, lc.joined());
         } else {
             int rc = enqueue_chunk<R, Geo>(c, lc, n, phi64, b, x, len, ru_filter, k == 0, sample, k & 1, s);
             if (rc) return rc;
@@ -1511,7 +1610,7 @@ static int solve_step_graph(hmc_ctx* c, const Launch<Geo>& lc, int n, double* ph
     int K = (int(1.1 * c->sg_last_iters) + 2 * chunk - 1) / chunk;
     K = std::min((K + 1) / 2 * 2, c->p.cg_maxit / chunk + 2);
     const auto key = std::make_tuple(K, drift_pi ? 1 : 0, (const void*)phi, (const void*)drift_pi, (const void*)b,
-                                     (const void*)x, n, c->generation, lc.pc ? 1 : 0, mixed ? 1 : 0, eps,
+                                     (const void*)x, n, c->generation, (lc.pc ? 1 : 0) + 2 * lc.joined(), mixed ? 1 : 0, eps,
                                      c->nunits);
     hmc_ctx::StepGraph* g = nullptr;
     for (auto& e : c->sgs)
@@ -1921,6 +2020,12 @@ static void pc_lds_attributes_r(size_t t) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_xy<R, true, Geo, MAXR>), a, int(xy));
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_t<R, Geo, false>), a, int(t));
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_t<R, Geo, true>), a, int(t));
+    if constexpr (std::is_same<Geo, GeoOne>::value) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_a<R, false, MAXR>), a, int(xy));
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_a<R, true, MAXR>), a, int(xy));
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_b<R, false, MAXR>), a, int(xy));
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_b<R, true, MAXR>), a, int(xy));
+    }
 }
 
 template <class Geo>

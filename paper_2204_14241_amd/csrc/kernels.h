@@ -524,6 +524,44 @@ struct CgVecs {
     C2<R>* z;       // preconditioned residual P r (the residual itself without preconditioner)
 };
 
+// The time-local part of M and its time link at the site (x, y) from a slice in LDS: at(d, c, yy) is
+// component c at row x + d, column yy (the caller knows how rows wrap); phi(tau) there given as
+// (f1, f2, f3) before the coupling and the staggered sign are applied; the time link is ts tt.  The
+// operations are those of dslash_site in their order.  cen receives the site's own value.
+template <typename R, bool NN2, class At>
+__device__ __forceinline__ void stencil_site_at(const At& at, int x, int y, int L, R f1, R f2, R f3, const Coef<R>& cf,
+                                                R ts, const C2<R> (&tt)[4], C2<R> (&o)[4], C2<R> (&cen)[4]) {
+    const int yp = y + 1 == L ? 0 : y + 1, ym = y == 0 ? L - 1 : y - 1;
+    const int ypp = y + 2 >= L ? y + 2 - L : y + 2, ymm = y < 2 ? y - 2 + L : y - 2;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cen[c] = at(0, c, y);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int a = c >> 1;
+        const C2<R> hx = add<R>(at(1, c, y), at(-1, c, y));
+        const C2<R> hy = add<R>(at(0, c, yp), at(0, c, ym));
+        C2<R> v = scl<R>(cf.diag[a], cen[c]);
+        v = axpy<R>(cf.hop[a][0], hx, v);
+        v = axpy<R>(cf.hop[a][1], hy, v);
+        v = axpy<R>(ts, tt[c], v);
+        if constexpr (NN2) {
+            v = axpy<R>(cf.hop2[a][0], add<R>(at(2, c, y), at(-2, c, y)), v);
+            v = axpy<R>(cf.hop2[a][1], add<R>(at(0, c, ypp), at(0, c, ymm)), v);
+        }
+        o[c] = v;
+    }
+    const R g = cf.cpl * R(((x + y) & 1) ? -1 : 1);
+    const R q1 = g * f1, q2 = g * f2, q3 = g * f3;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const C2<R> u = cen[2 * (1 - a)], w = cen[2 * (1 - a) + 1];
+        o[2 * a].x += q3 * u.x + q1 * w.x + q2 * w.y;
+        o[2 * a].y += q3 * u.y + q1 * w.y - q2 * w.x;
+        o[2 * a + 1].x += q1 * u.x - q2 * u.y - q3 * w.x;
+        o[2 * a + 1].y += q1 * u.y + q2 * u.x - q3 * w.y;
+    }
+}
+
 // Store this workgroup's partial (thread 0) after a block reduction.
 __device__ __forceinline__ void store_partial(const CgCtl& c, int kind, const UPos& p, double v) {
     double a[1] = {v};

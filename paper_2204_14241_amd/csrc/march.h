@@ -146,35 +146,8 @@ __device__ __forceinline__ void stencil_site_lds(const double2* __restrict__ chi
                                                  double ts, const double2 (&tt)[4], double2 (&o)[4],
                                                  double2 (&cen)[4]) {
     const int rowc = 4 * L;
-    const int yp = y + 1 == L ? 0 : y + 1, ym = y == 0 ? L - 1 : y - 1;
-    const int ypp = y + 2 >= L ? y + 2 - L : y + 2, ymm = y < 2 ? y - 2 + L : y - 2;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) cen[c] = chi[r * rowc + c * L + y];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int a = c >> 1;
-        const double2 hx = add<double>(chi[(r + 1) * rowc + c * L + y], chi[(r - 1) * rowc + c * L + y]);
-        const double2 hy = add<double>(chi[r * rowc + c * L + yp], chi[r * rowc + c * L + ym]);
-        double2 v = scl<double>(cf.diag[a], cen[c]);
-        v = axpy<double>(cf.hop[a][0], hx, v);
-        v = axpy<double>(cf.hop[a][1], hy, v);
-        v = axpy<double>(ts, tt[c], v);
-        if constexpr (NN2) {
-            v = axpy<double>(cf.hop2[a][0], add<double>(chi[(r + 2) * rowc + c * L + y], chi[(r - 2) * rowc + c * L + y]), v);
-            v = axpy<double>(cf.hop2[a][1], add<double>(chi[r * rowc + c * L + ypp], chi[r * rowc + c * L + ymm]), v);
-        }
-        o[c] = v;
-    }
-    const double g = cf.cpl * double(((x + y) & 1) ? -1 : 1);
-    const double q1 = g * f1, q2 = g * f2, q3 = g * f3;
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const double2 u = cen[2 * (1 - a)], w = cen[2 * (1 - a) + 1];
-        o[2 * a].x += q3 * u.x + q1 * w.x + q2 * w.y;
-        o[2 * a].y += q3 * u.y + q1 * w.y - q2 * w.x;
-        o[2 * a + 1].x += q1 * u.x - q2 * u.y - q3 * w.x;
-        o[2 * a + 1].y += q1 * u.y + q2 * u.x - q3 * w.y;
-    }
+    stencil_site_at<double, NN2>([&](int d, int c, int yy) __attribute__((always_inline)) { return chi[(r + d) * rowc + c * L + yy]; },
+                                 x, y, L, f1, f2, f3, cf, ts, tt, o, cen);
 }
 
 __device__ __forceinline__ void mdag_site_lds(const double2* __restrict__ chi, int r, int x, int y, int s,

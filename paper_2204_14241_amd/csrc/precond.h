@@ -323,7 +323,9 @@ void k_pc_t(CgCtl ctl, Geo geo, C2<R>* z,
     const Lat& lat = pos.lat;
     const int L = lat.L, Lt = lat.Lt, LL = lat.LL;
     CgState S;
-    cg_finalize(ctl, pos, 0, S);
+    // after k_pc_b (pcstep.h), which transforms before |r|^2 is known, a residual that has converged
+    // needs no z
+    if (cg_finalize(ctl, pos, 0, S) == PEND_RR && S.mode != CG_ACTIVE) S.zstage = 0;
     const bool work = S.pc && S.mode == CG_ACTIVE && S.zstage == 1;
     if (work) {
         S.zstage = 2;
