@@ -594,6 +594,38 @@ static int batch_slices(const hmc_ctx* c, int pi) {
     return 1;
 }
 
+// The workgroups of a batch launch, unit by unit, in the order that xcd_remap hands to the XCDs: an
+// eighth of every unit to each (consecutive workgroups, which share rows and slices in that XCD's
+// L2), larger lattices first.  Unit by unit, an XCD had a few units' workgroups to itself: unlike
+// amounts of work, and once some units are finished XCDs with nothing to do.  Twelve preconditioned
+// chains of 12 x 12 x 40 to 48 x 48 x 80, four vectors each: the tau pass 56 -> 47 us with all of them running,
+// 46 -> 18 with the three longest left, step A 110 -> 90 and 51 -> 36.
+static std::vector<int2> spread_units(const std::vector<int2>& by_unit, const std::vector<Lat>& lats, int nrhs) {
+    std::vector<std::pair<size_t, size_t>> runs;       // [first, end) of each unit
+    for (size_t i = 0; i < by_unit.size(); ++i) {
+        if (i == 0 || by_unit[i].x != by_unit[i - 1].x) runs.emplace_back(i, i);
+        runs.back().second = i + 1;
+    }
+    std::stable_sort(runs.begin(), runs.end(), [&](const auto& a, const auto& b) {
+        return lats[size_t(by_unit[a.first].x / nrhs)].vol > lats[size_t(by_unit[b.first].x / nrhs)].vol;
+    });
+    std::vector<int2> of[kNumXcd];
+    size_t turn = 0;      // the XCD that takes the next workgroup beyond a unit's equal shares
+    for (const auto& r : runs) {
+        const size_t n = r.second - r.first, share = n / kNumXcd, over = n % kNumXcd;
+        size_t at = r.first;
+        for (size_t g = 0; g < size_t(kNumXcd); ++g) {
+            const size_t mine = share + ((g + kNumXcd - turn) % kNumXcd < over ? 1 : 0);
+            of[g].insert(of[g].end(), by_unit.begin() + long(at), by_unit.begin() + long(at + mine));
+            at += mine;
+        }
+        turn = (turn + over) % kNumXcd;
+    }
+    std::vector<int2> out;
+    for (const auto& o : of) out.insert(out.end(), o.begin(), o.end());
+    return out;
+}
+
 // Batch: (re)write the unit and block tables of one precision's launch shape, with the march
 // cuts of step A (this precision) and of the reliable update (FP64).
 static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
@@ -634,6 +666,9 @@ static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
             for (int w = 0; w < d.rparts; ++w) rblocks.push_back(make_int2(u, w));
         }
     }
+    blocks = spread_units(blocks, b.lats, b.nrhs);
+    mblocks = spread_units(mblocks, b.lats, b.nrhs);
+    rblocks = spread_units(rblocks, b.lats, b.nrhs);
     b.nblocks[pi] = int(blocks.size());
     // a launch marches every unit or none
     b.mgrid[pi] = m_ok ? int(mblocks.size()) : 0;
@@ -2068,6 +2103,10 @@ static int upload_pc(hmc_ctx* c) {
                 for (int r = 0; r < 4 * pc_groups(l.LL, kPcCols); ++r) t[0].push_back(make_int2(u, r));
                 for (int r = 0; r < 4 * pc_groups(l.LL, kPcCols); ++r) t[1].push_back(make_int2(u, r));
             }
+        }
+        for (int pi = 0; pi < 2; ++pi) {
+            xy[pi] = spread_units(xy[pi], b.lats, b.nrhs);
+            t[pi] = spread_units(t[pi], b.lats, b.nrhs);
         }
         for (int pi = 0; pi < 2; ++pi)
             HIPCHK(hipMemcpy(b.pxy_blocks[pi], xy[pi].data(), sizeof(int2) * xy[pi].size(), hipMemcpyHostToDevice));
