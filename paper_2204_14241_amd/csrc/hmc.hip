@@ -438,7 +438,7 @@ static size_t ws_layout(hmc_ctx* c, char* base) {
     char* tr = take(2 * sp64);
     char* bos = take(2 * 3 * PS * sizeof(double));
     char* f32 = take(3 * PS * sizeof(float));
-    char* mp = c->is_batch ? nullptr : take(sizeof(double) * 3 * size_t(std::max(pc_groups(c->lat.LL, pc_ncol<double>()), 256)));
+    char* mp = c->is_batch ? nullptr : take(sizeof(double) * 3 * size_t(std::max(pc_groups(c->L * (c->L / 2 + 1), kMtCols), 256)));
     char* pw = c->is_batch ? nullptr : take(3 * PS * sizeof(double));
     char *un0 = nullptr, *un1 = nullptr, *bl0 = nullptr, *bl1 = nullptr, *ch = nullptr,
          *cb = nullptr, *cf = nullptr, *cs = nullptr, *pxy0 = nullptr, *pxy1 = nullptr, *pt0 = nullptr, *pt1 = nullptr,
@@ -1856,15 +1856,16 @@ static int read_slots(hmc_ctx* c, hipStream_t s) {
 template <int XY, int T>
 static int metric_passes_r(hmc_ctx* c, const double* in, double* out, int add, double h, int mul, int red,
                            double rs, double* acc, int slot, hipStream_t s, int acc_add) {
-    const MetricGeo g{c->lat.L, c->lat.Lt, c->lat.LL, c->lat.vol, c->mt_cut.pitch};
+    const int hw = c->L / 2 + 1, hl = c->L * hw;
+    const MetricGeo g{c->lat.L, c->lat.Lt, c->lat.LL, c->lat.vol, c->mt_cut.pitch, hw, hl, kMtCols};
     double2* scr = c->t64;
-    const int nslice = 3 * g.Lt, ngrp = 3 * pc_groups(g.LL, pc_ncol<double>());
-    const size_t mt_lds = slice_lds<double>(c->mt_cut, g.L);
+    const int nslice = 3 * ((g.Lt + 1) / 2), ngrp = 3 * pc_groups(hl, g.ncol);
+    const size_t mt_lds = mt_xy_lds(g.L, g.pitch);
     const int mt_threads = slice_threads(c->mt_cut, g.L);
     hipLaunchKernelGGL((k_mt_xy<false, XY>), dim3(nslice), dim3(mt_threads), mt_lds, s, g, in, scr,
                        static_cast<double*>(nullptr), 0, 0.0, c->blob);
     LAUNCHCHK();
-    hipLaunchKernelGGL((k_mt_t<T>), dim3(ngrp), dim3(kPcBlock), c->lds_mt_t, s, g, scr, c->sigma, mul, red, rs,
+    hipLaunchKernelGGL((k_mt_t<T>), dim3(ngrp), dim3(ngrp >= 512 ? kMtThreads : kPcBlock), mt_t_lds(g.L, g.Lt, g.ncol), s, g, scr, c->sigma, mul, red, rs,
                        acc, acc_add, red ? c->mpart : static_cast<double*>(nullptr), c->blob);
     LAUNCHCHK();
     if (red) {
@@ -2032,7 +2033,7 @@ static void pc_setup(hmc_ctx* c) {
                        c->lds_t[pi] <= size_t(maxlds);
     if (!c->is_batch) {
         const Lat& l = c->lat;
-        c->lds_mt_t = size_t(l.Lt) * (pc_ncol<double>() + 1) * sizeof(double2) + size_t(l.Lt + l.L) * sizeof(int);
+        c->lds_mt_t = mt_t_lds(l.L, l.Lt, pc_ncol<double>());   // the limit on N_tau
         c->metric_ok = plans && least[0] <= size_t(maxlds) && c->lds_mt_t <= size_t(maxlds);
         c->mt_cut = SliceCut{1, slice_pitch<double>(c->L, 1)};
     }
@@ -2116,12 +2117,13 @@ static int upload_pc(hmc_ctx* c) {
     } else {
         pc_lds_attributes<GeoOne>(c);
         if (c->metric_ok) {
+            const size_t mt_lds = mt_xy_lds(c->L, c->mt_cut.pitch);
             const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, kFftNarrow>), a, int(kPcLdsMost));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, kFftNarrow>), a, int(kPcLdsMost));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, kFftNarrow>), a, int(mt_lds));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, kFftNarrow>), a, int(mt_lds));
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_t<kFftNarrow>), a, int(c->lds_mt_t));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, kFftMaxRadix>), a, int(kPcLdsMost));
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, kFftMaxRadix>), a, int(kPcLdsMost));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<false, kFftMaxRadix>), a, int(mt_lds));
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_xy<true, kFftMaxRadix>), a, int(mt_lds));
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mt_t<kFftMaxRadix>), a, int(c->lds_mt_t));
             (void)hipGetLastError();
         }
