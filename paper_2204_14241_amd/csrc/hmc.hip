@@ -1583,10 +1583,12 @@ static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64,
     // when the records (or, before the first ones, the last solve) say that the chunk in flight
     // should be the last: a chunk past the end is some hundred launches that do nothing, 2-5 us each,
     // where waiting costs 30 us if the estimate was wrong.  In FP64 a chunk's length is free
-    // (nothing but the status check happens at its end): the last one is cut to the estimate.
+    // (nothing but the status check happens at its end): the last one is cut to the estimate.  Not
+    // where step A is joined: a chunk's first step A stands alone and sums |t|^2 in another order, so
+    // the chunks' lengths must not depend on earlier solves.
     for (; !done_early;) {
         int len = chunk;
-        if (!mixed && !use_graphs && left > 0) len = std::max(8, std::min(chunk, left + 4));
+        if (!mixed && !use_graphs && !lc.join_a && left > 0) len = std::max(8, std::min(chunk, left + 4));
         if (use_graphs) {
             HIPCHK(hipGraphLaunch(c->cgg[mixed ? 1 : 0].exec[k == 0 ? 0 : 1], s));
             c->seq += chunk_launches(chunk, lc.pc, lc.joined());

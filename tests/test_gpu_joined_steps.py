@@ -50,3 +50,24 @@ def test_joined_steps(hip, L, Lt, n, nnn, precision):
     assert st.status == rt.status and list(st.iterations) == list(rt.iterations)
     bar = 1e-12 if precision == "fp64" else 2e-5
     assert float((x - y).norm()) <= bar * float(y.norm())
+
+
+# counts of iterations over one status chunk: step A joined, step B alone
+@pytest.mark.parametrize("L,Lt,n", [(16, 80, 2), (28, 54, 3), (28, 60, 1)])
+def test_joined_steps_do_not_depend_on_earlier_solves_or_graphs(hip, L, Lt, n):
+    import torch
+    print(f"joined steps repeated {L}x{L}x{Lt} n={n}", flush=True)
+    g = S.rng(13 * L + Lt)
+    phi, soft = (torch.from_numpy(S.draw_phi(g, L, Lt, v)).cuda() for v in (0.5, 0.05))
+    b = torch.from_numpy(S.draw_spinor(g, L, Lt, n)).cuda()
+    h = hip.HMC(L, Lt, n_pf=n, cg_tol=1e-10, precond="fourier")
+    x, st = h.cg_solve(phi, b)
+    again, _ = h.cg_solve(phi, b)
+    short = h.cg_solve(soft, b)[1]
+    after, at = h.cg_solve(phi, b)
+    assert max(st.iterations) > 40 > max(short.iterations)
+    h.set_graphs(True)
+    graph, gt = h.cg_solve(phi, b)
+    for y in (again, after, graph):
+        assert torch.equal(x, y)
+    assert list(at.iterations) == list(gt.iterations) == list(st.iterations)
