@@ -404,7 +404,7 @@ int hmc_get_mdm_shape(const hmc_ctx* ctx, int precision, int n, int* rows, int* 
  * batch: hmc_batch_set_cg_march); lattices whose band does not fit (rows + 2 rows, or rows + 4
  * with the two-site hops, of one thread per element in FP64 or per pair in FP32, at most 512
  * threads) keep the tile kernels.  The FP64 setting also cuts the reliable update's FP64
- * stencils into marches (nearest-neighbour operator). */
+ * stencils into marches. */
 int hmc_set_cg_march(hmc_ctx* ctx, int precision, int rows, int slices);
 /* The cut in use for `precision` (host ints; rows 0: the tile kernels); the default one is that of
  * max_rhs right-hand sides. */

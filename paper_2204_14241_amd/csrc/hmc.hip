@@ -966,19 +966,21 @@ static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
         l.ps_threads = std::min(kPcBlock, (c->lat.LL + 63) / 64 * 64);
         for (int b = 0; b < 2; ++b) l.ps_lds[b] = pc_step_lds<R>(c->L, c->L + 1, b != 0);
     }
-    // the reliable update's FP64 marches: one thread per element of the band and its two
-    // neighbour rows, as the FP64 step-A march
-    if (l.cgm_per_unit > 0 && rcut.rows > 0 && !l.nn2) {
-        const int rows = std::max(1, std::min(rcut.rows, kMarchCgThreads / c->L - 2));
-        const size_t lds = march_cg_lds<double>(rows, c->L);
-        if ((rows + 2) * c->L <= kMarchCgThreads && lds <= (size_t(64) << 10)) {
+    // the reliable update's FP64 marches: one thread per element of the band and the rows beside
+    // it, as the FP64 step-A march (with the two-site hops at 80 x 80 x 200, FP32 solve: 116 us for both
+    // against 186 as tile kernels, which read each neighbour again)
+    if (l.cgm_per_unit > 0 && rcut.rows > 0) {
+        const int H = l.nn2 ? 2 : 1;
+        const int rows = std::max(1, std::min(rcut.rows, kMarchCgThreads / c->L - 2 * H));
+        const size_t lds = march_cg_lds<double>(rows + 2 * H - 2, c->L);
+        if ((rows + 2 * H) * c->L <= kMarchCgThreads && lds <= (size_t(64) << 10)) {
             const int nband = (c->L + std::min(rows, c->L) - 1) / std::min(rows, c->L);
             int seg = rcut.slices;
             if (seg <= 0) seg = std::max(2, (c->Lt * nband * n + 255) / 256);
             l.rum = make_march_plan(c->L, c->Lt, rows, seg);
             l.rum_per_unit = l.rum.nband * l.rum.nseg;
             if (l.rum_per_unit > c->pstride) l.rum_per_unit = 0;
-            l.rum_threads = ((std::min(rows, c->L) + 2) * c->L + 63) / 64 * 64;
+            l.rum_threads = ((std::min(rows, c->L) + 2 * H) * c->L + 63) / 64 * 64;
             l.rum_lds = lds;
         }
     }
@@ -1362,15 +1364,21 @@ static int enqueue_chunk(hmc_ctx* c, const Launch<Geo>& lc, int n, const double*
     }
     const bool ru_march = rgrid > 0;
     if (ru_march) {
-        auto go = [&](auto mg) {
+        auto go = [&](auto mg, auto nn2) {
             using MG = decltype(mg);
-            hipLaunchKernelGGL((k_ru_apply_march<MG>), dim3(rgrid), dim3(rthreads), rlds, s, next_ctl(c, PEND_NONE), mg,
-                               x, c->t64, phi64, c->cf64, filter);
-            hipLaunchKernelGGL((k_ru_resid_march<R, MG>), dim3(rgrid), dim3(rthreads), rlds, s, next_ctl(c, PEND_NONE),
-                               mg, b, c->t64, phi64, c->cf64, v.r, filter);
+            constexpr bool N2 = decltype(nn2)::value;
+            hipLaunchKernelGGL((k_ru_apply_march<MG, N2>), dim3(rgrid), dim3(rthreads), rlds, s, next_ctl(c, PEND_NONE),
+                               mg, x, c->t64, phi64, c->cf64, filter);
+            hipLaunchKernelGGL((k_ru_resid_march<R, MG, N2>), dim3(rgrid), dim3(rthreads), rlds, s,
+                               next_ctl(c, PEND_NONE), mg, b, c->t64, phi64, c->cf64, v.r, filter);
         };
-        if constexpr (std::is_same<Geo, GeoOne>::value) go(MGeoOne{geo.lat, lc.rum, geo.bpr, c->pstride});
-        else go(lc.br);
+        if constexpr (std::is_same<Geo, GeoOne>::value) {
+            const MGeoOne mg{geo.lat, lc.rum, geo.bpr, c->pstride};
+            if (lc.nn2) go(mg, std::true_type{});
+            else go(mg, std::false_type{});
+        } else {
+            go(lc.br, std::false_type{});    // batches march the nearest-neighbour operator only
+        }
         LAUNCHCHK();
         c->next_nparts = rparts;
     }

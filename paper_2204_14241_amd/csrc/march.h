@@ -15,8 +15,8 @@
 // consecutive segments and the rows beside a band are read through the same L2.  A second form
 // of the normal operator takes one slice per workgroup and forms chi(tau - 1) itself.
 //
-// The one-pass normal operator and the reliable-update marches take the nearest-neighbour
-// operator only; step A also takes the production model's two-site hops, with two rows beside
+// The one-pass normal operator takes the nearest-neighbour operator only; steps A and B and the
+// reliable-update marches also take the production model's two-site hops, with two rows beside
 // the band on either side.  The arithmetic per site is that of the two-pass kernels, in the same
 // order.
 #pragma once
@@ -795,7 +795,7 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_cg_b_march(CgCtl ctl, MG mg
 // and the rows beside it goes to LDS while M at tau is formed from the previous slice's copy,
 // the time link taken from the thread's own element of tau + 1.  Reads x64 and phi once (plus
 // the rows beside each band and one slice per segment), writes t64 once.
-template <class MG>
+template <class MG, bool NN2>
 __global__ __launch_bounds__(kMarchCgThreads) void k_ru_apply_march(CgCtl ctl, MG mg, const double2* __restrict__ x64,
                                                                     double2* __restrict__ t64,
                                                                     const double* __restrict__ phi_base,
@@ -808,6 +808,7 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_apply_march(CgCtl ctl, M
     const UPos& pos = w.pos;
     const double* phi = phi_base + pos.phioff;
     const int L = lat.L, Lt = lat.Lt, LL = lat.LL, vol = lat.vol, rowc = 4 * L;
+    constexpr int H = NN2 ? 2 : 1;    // rows beside the band on either side
     CgState S;
     cg_finalize(ctl, pos, w.nparts_in, S);
     cg_publish(ctl, pos, S);
@@ -816,12 +817,12 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_apply_march(CgCtl ctl, M
     const double2* xin = x64 + off;
     double2* t = t64 + off;
     double2* cur = reinterpret_cast<double2*>(march_smem);
-    double2* nxt = cur + size_t(mp.R + 2) * rowc;
-    const int e = threadIdx.x, nh = (mpos.nr + 2) * L;
+    double2* nxt = cur + size_t(mp.R + 2 * H) * rowc;
+    const int e = threadIdx.x, nh = (mpos.nr + 2 * H) * L;
     const bool act = e < nh;
     const int lr = act ? e / L : 0, y = act ? e - lr * L : 0;
-    const int xrow = wrap_row(mpos.x0 - 1 + lr, L);
-    const bool inner = act && lr >= 1 && lr <= mpos.nr;
+    const int xrow = wrap_row(mpos.x0 - H + lr, L);
+    const bool inner = act && lr >= H && lr < mpos.nr + H;
     const int ro = xrow * L + y;
     double2 rv[4];
     double f1 = 0.0, f2 = 0.0, f3 = 0.0;
@@ -865,7 +866,7 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_apply_march(CgCtl ctl, M
         __syncthreads();
         if (inner) {
             double2 o[4], cen[4];
-            stencil_site_lds(cur, lr, xrow, y, L, g1, g2, g3, cf, tau == Lt - 1 ? -1.0 : 1.0, vn, o, cen);
+            stencil_site_lds<NN2>(cur, lr, xrow, y, L, g1, g2, g3, cf, tau == Lt - 1 ? -1.0 : 1.0, vn, o, cen);
 #pragma unroll
             for (int c = 0; c < 4; ++c) t[size_t(c) * vol + size_t(tau) * LL + ro] = o[c];
         }
@@ -881,7 +882,7 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_apply_march(CgCtl ctl, M
 // the site itself: each slice's own element is kept in registers for the next.  LDS holds
 // t64(tau) on the band's rows and the rows beside it, alternating between two buffers so that
 // one barrier per slice suffices; the next slice's loads are in flight meanwhile.
-template <typename R, class MG>
+template <typename R, class MG, bool NN2>
 __global__ __launch_bounds__(kMarchCgThreads) void k_ru_resid_march(CgCtl ctl, MG mg, const double2* __restrict__ b,
                                                                     const double2* __restrict__ t64,
                                                                     const double* __restrict__ phi_base,
@@ -894,6 +895,7 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_resid_march(CgCtl ctl, M
     const UPos& pos = w.pos;
     const double* phi = phi_base + pos.phioff;
     const int L = lat.L, Lt = lat.Lt, LL = lat.LL, vol = lat.vol, rowc = 4 * L;
+    constexpr int H = NN2 ? 2 : 1;    // rows beside the band on either side
     CgState S;
     cg_finalize(ctl, pos, w.nparts_in, S);
     const bool work = ((1 << S.mode) & filter) != 0;
@@ -905,12 +907,12 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_resid_march(CgCtl ctl, M
     const double2* bb = b + off;
     C2<R>* rr = r + off;
     double2* buf0 = reinterpret_cast<double2*>(march_smem);
-    double2* buf1 = buf0 + size_t(mp.R + 2) * rowc;
-    const int e = threadIdx.x, nh = (mpos.nr + 2) * L;
+    double2* buf1 = buf0 + size_t(mp.R + 2 * H) * rowc;
+    const int e = threadIdx.x, nh = (mpos.nr + 2 * H) * L;
     const bool act = e < nh;
     const int lr = act ? e / L : 0, y = act ? e - lr * L : 0;
-    const int xrow = wrap_row(mpos.x0 - 1 + lr, L);
-    const bool inner = act && lr >= 1 && lr <= mpos.nr;
+    const int xrow = wrap_row(mpos.x0 - H + lr, L);
+    const bool inner = act && lr >= H && lr < mpos.nr + H;
     const int ro = xrow * L + y;
     // defined on every thread (a conditionally loaded array would be kept in scratch memory)
     double2 rv[4], bv[4], prev[4];
@@ -959,7 +961,7 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_resid_march(CgCtl ctl, M
         __syncthreads();
         if (inner) {
             double2 o[4], cen[4];
-            stencil_site_lds(cur, lr, xrow, y, L, g1, g2, g3, cf, tau == 0 ? -1.0 : 1.0, prev, o, cen);
+            stencil_site_lds<NN2>(cur, lr, xrow, y, L, g1, g2, g3, cf, tau == 0 ? -1.0 : 1.0, prev, o, cen);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const double2 d = sub<double>(bt[c], o[c]);
