@@ -32,7 +32,7 @@
 // table, and small slices share a workgroup (slice_cut in hmc.hip).  Per pass, before -> after:
 // FP32 80 x 80 x 200 33.4 -> 25.5 us; FP32 16 x 16 x 80, four vectors, 14.0 -> 6.2 us; FP64 28 x 28 x 75, two
 // vectors, 28.2 -> 9.7 us; FP64 60 x 60 x 160 41.9 -> 24.4 us; FP32, twelve chains of 12 to 48, four
-// vectors each, 156 -> 49 us.  Loading the first butterfly's inputs before the record is
+// vectors each, all running, 172 -> 56 us.  Loading the first butterfly's inputs before the record is
 // reduced gained nothing (28.3 us at 80 x 80 x 200: the registers cost a workgroup per CU), nor did 256-
 // and 384-thread workgroups (33 and 30 us).
 #pragma once
