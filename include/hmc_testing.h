@@ -52,6 +52,10 @@ int hmc_test_fft_freq(int n, int pos);
 int hmc_test_precond(int L, int L_tau, double dtau, const hmc_params* params, const double* in,
                      double* out, double* rz);
 
+/* Where the one-kernel solve of a small lattice goes after a true residual |r|^2 = rt (the update at
+ * the iteration cap if capped), with iters iterations done of maxit: 0 on, 3 done, 4 stopped, 5 failed. */
+int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit);
+
 /* One application z = P r of the Fourier preconditioner P = (K K^dagger)^{-1} of Methods C
  * (Eq. 23-26) ON THE GPU, by the kernels a preconditioned solve runs (it is the only entry
  * point here that touches a device).  ctx: a one-lattice context with its workspace set (its

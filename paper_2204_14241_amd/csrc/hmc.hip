@@ -73,6 +73,7 @@ int fail(int code, const char* fmt, ...) {
 size_t align_up(size_t n, size_t a) { return (n + a - 1) / a * a; }
 
 constexpr int kCheckEvery = 32;     // FP64 CG: most iterations between host status reads
+static_assert(kSmallPast == 4 * kCheckEvery, "the one-kernel solve gives up where the host loop does");
 constexpr int kSlots = 32;          // device scalars (energies, actions)
 constexpr int kChainSlots = 8;      // per-lattice scalars in batch mode
 constexpr int kDefaultBpr64 = 1024; // default CG workgroups per right-hand side, FP64
@@ -2705,6 +2706,10 @@ int hmc_test_fft(int n, int inverse, const double* in, double* out) {
         out[2 * i + 1] = buf[size_t(i)].y;
     }
     return 0;
+}
+
+int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit) {
+    return small_next(rt, stop_rr, capped != 0, iters, maxit);
 }
 
 int hmc_test_fft_freq(int n, int pos) {

@@ -55,7 +55,17 @@ __device__ __forceinline__ void small_stencil(const double2* buf, const Lat& lat
     }
 }
 
-
+// Where a solve goes after its true residual rt: done, stopped, or on (CG_ACTIVE).  capped: the update
+// is the one at the iteration cap.  A solve whose iterated residual passes and whose true one does
+// not may go on past the cap, as the chunked solver lets it; with a tolerance below FP64's reach it
+// could do so for ever, so it is stopped kSmallPast iterations past it, where the chunked solver's host
+// loop gives up.
+constexpr int kSmallPast = 128;
+__host__ __device__ inline int small_next(double rt, double stop_rr, bool capped, int iters, int maxit) {
+    if (!(rt - rt == 0.0)) return CG_FAILED;
+    if (rt <= stop_rr) return CG_DONE;
+    return capped || iters - kSmallPast >= maxit ? CG_STOPPED : CG_ACTIVE;
+}
 
 // Solve (M^dagger M) x_k = b_k, k = blockIdx.x, in FP64 from x = 0 (the algebra and the stopping rules
 // of the chunked solver: k_cg_a, k_cg_b and the state machine of cg_finalize).  st[k] receives the
@@ -158,13 +168,8 @@ __global__ __launch_bounds__(kSmallSites) void k_cg_small(Lat lat, const double2
         const double rt = total(norm4(r));
         rr_true = rt;
         n_ru += 1;
-        if (!finite(rt)) {
-            mode = CG_FAILED;
-        } else if (rt <= stop_rr) {
-            mode = CG_DONE;
-        } else if (last) {
-            mode = CG_STOPPED;
-        } else {
+        mode = small_next(rt, stop_rr, last, iters, maxit);
+        if (mode == CG_ACTIVE) {
             beta = rt / rz_prev;
             rz = rr = rt;
         }

@@ -680,6 +680,11 @@ def test_fft_freq(n, pos):
     return _lib.load().hmc_test_fft_freq(n, pos)
 
 
+def test_small_next(rt, stop_rr, capped, iters, maxit):
+    """Where the one-kernel solve goes after a true residual: 0 on, 3 done, 4 stopped, 5 failed."""
+    return _lib.load().hmc_test_small_next(rt, stop_rr, int(capped), iters, maxit)
+
+
 def test_precond(L, Lt, v, dtau=0.1, model=None):
     """The kernels' three-pass Fourier preconditioner run on the host in FP64 on one spinor
     (complex128, 4 * L_tau * L * L values).  Returns (P v, <v, P v>)."""
