@@ -80,7 +80,7 @@ struct FftPlan {
     int nst;                    // number of radix stages
     FftStage st[kFftMaxStages]; // stage 0 (outermost) ... nst - 1
     Div32 dn;                   // division by n
-    Div32 dout;                 // division by n * (n / last radix): see fft_slice_pos
+    Div32 dout;                 // slice lengths: division by n * (n / last radix), see fft_slice_pos
 };
 
 // The radices of length n: the fewest stages, of those the smallest largest radix (then the
@@ -127,7 +127,8 @@ inline bool make_fft_plan(int n, FftPlan& p) {
         len /= r[s];
     }
     p.dn.init(uint32_t(n));
-    p.dout.init(uint32_t(p.nst > 0 ? n * (n / r[p.nst - 1]) : 1));
+    // an L only: the square of a time extent does not fit 32 bits
+    p.dout.init(uint32_t(p.nst > 0 && n <= kMaxL ? n * (n / r[p.nst - 1]) : 1));
     return true;
 }
 
