@@ -56,6 +56,15 @@ int hmc_test_precond(int L, int L_tau, double dtau, const hmc_params* params, co
  * the iteration cap if capped), with iters iterations done of maxit: 0 on, 3 done, 4 stopped, 5 failed. */
 int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit);
 
+/* The kernels a solve of n right-hand sides would run with the context's present settings: the sum of
+ * the values below (steps A and B joined with the preconditioner's slice passes, step A a march where it
+ * stands alone), or -1 for a bad argument. */
+#define HMC_TEST_PATH_ONE_KERNEL 1
+#define HMC_TEST_PATH_JOIN_A     2
+#define HMC_TEST_PATH_JOIN_B     4
+#define HMC_TEST_PATH_MARCH      8
+int hmc_test_solve_path(const hmc_ctx* ctx, int n);
+
 /* One application z = P r of the Fourier preconditioner P = (K K^dagger)^{-1} of Methods C
  * (Eq. 23-26) ON THE GPU, by the kernels a preconditioned solve runs (it is the only entry
  * point here that touches a device).  ctx: a one-lattice context with its workspace set (its

@@ -2708,6 +2708,16 @@ int hmc_test_fft(int n, int inverse, const double* in, double* out) {
     return 0;
 }
 
+int hmc_test_solve_path(const hmc_ctx* c, int n) {
+    if (c == nullptr || c->is_batch || n < 1 || n > c->cap) return -1;
+    auto path = [&](const Launch<GeoOne>& l, bool fp64) {
+        if (fp64 && small_lattice(c, l.pc)) return int(HMC_TEST_PATH_ONE_KERNEL);
+        return (l.join_a ? HMC_TEST_PATH_JOIN_A : 0) | (l.join_b ? HMC_TEST_PATH_JOIN_B : 0) |
+               (l.cgm_per_unit > 0 ? HMC_TEST_PATH_MARCH : 0);
+    };
+    return c->p.precision == HMC_MIXED ? path(launch_one<float>(c, n), false) : path(launch_one<double>(c, n), true);
+}
+
 int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit) {
     return small_next(rt, stop_rr, capped != 0, iters, maxit);
 }

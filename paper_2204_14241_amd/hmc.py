@@ -327,6 +327,14 @@ class HMC:
                    _ptr(z), n, rz, _stream())
         return z, list(rz)
 
+    def solve_path(self, n=1):
+        """The kernels a solve of n right-hand sides would run (hmc_test_solve_path), as a set of
+        "one_kernel", "join_a", "join_b", "march"."""
+        v = self.lib.hmc_test_solve_path(self._ctx, int(n))
+        if v < 0:
+            raise ValueError("n outside [1, max_rhs]")
+        return {k for i, k in enumerate(("one_kernel", "join_a", "join_b", "march")) if v >> i & 1}
+
     def apply_into(self, name, phi, psi, out, n):
         """Raw launch for benchmarks: no allocation, no checks beyond the library's."""
         self._call(name, _ptr(phi), _ptr(psi), _ptr(out), n, _stream())
