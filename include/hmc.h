@@ -455,7 +455,9 @@ typedef struct hmc_tune_result {
  * $HOME/.cache/hmc/tune.txt (HMC_TUNE_CACHE=off disables it).  hmc_create applies a cached
  * choice; hmc_autotune with the variable HMC_TUNE_REUSE=1 returns a cached choice without
  * timing.  Uses the context's workspace (no other allocation); the run parameters are restored
- * afterwards.  Synchronises the stream.  Errors: as hmc_cg_solve. */
+ * afterwards.  The times are those of the separate kernels: solves that run as one kernel or with
+ * joined steps (hmc_set_cg_march) go on doing so whatever is chosen, and take the chosen shape only
+ * for what stands alone in them.  Synchronises the stream.  Errors: as hmc_cg_solve. */
 int hmc_autotune(hmc_ctx* ctx, const double* phi, const void* b, int n, hmc_tune_result* out,
                  void* stream);
 int hmc_get_kernel_times(const hmc_ctx* ctx, hmc_kernel_times* out);

@@ -960,9 +960,10 @@ static Launch<GeoOne> launch_one(const hmc_ctx* c, int n) {
             l.cgm_lds = lds;
         }
     }
-    if (l.pc && l.cgm_per_unit > 0 && l.cgbm) {
-        l.join_a = join_step<R>(c, n, false);
+    if (l.pc) {
+        // whatever shape the autotuner chose for the separate kernels: the joined ones do not use it
         l.join_b = join_step<R>(c, n, true);
+        l.join_a = l.join_b && join_step<R>(c, n, false);
         l.ps = GeoOne{c->lat, c->Lt, c->Lt, c->pstride, SliceCut{1, c->L + 1}};
         l.ps_threads = std::min(kPcBlock, (c->lat.LL + 63) / 64 * 64);
         for (int b = 0; b < 2; ++b) l.ps_lds[b] = pc_step_lds<R>(c->L, c->L + 1, b != 0);
@@ -1188,6 +1189,29 @@ static void launch_step_march(hmc_ctx* c, const Launch<Geo>& lc, bool step_b, co
     }
 }
 
+// Step A of a preconditioned solve whose step B is joined with its slice pass: the march or the tile
+// kernel, whichever the launch shape says.  Leaves the count of its partials for step B.
+template <typename R>
+static int enqueue_step_a(hmc_ctx* c, const Launch<GeoOne>& lc, int n, const CgVecs<R>& v, const R* phik,
+                          const Coef<R>& cf, hipStream_t s) {
+    const CgCtl ka = next_ctl(c, PEND_NONE);
+    if (lc.cgm_per_unit > 0) {
+        launch_step_march<R, GeoOne>(c, lc, false, ka, v, phik, cf, lc.cgm_per_unit * n, lc.cgm_threads, lc.cgm_lds,
+                                     nullptr, s);
+        c->next_nparts = lc.cgm_per_unit;
+    } else {
+        if constexpr (sizeof(R) == sizeof(float))
+            HMC_LAUNCH_NN2(lc.nn2, (k_cg_a2<GeoOne, true>), (k_cg_a2<GeoOne, false>), dim3(lc.ncg), dim3(kBlock), 0, s, ka,
+                           lc.cg, v, phik, cf);
+        else
+            HMC_LAUNCH_NN2(lc.nn2, (k_cg_a<R, GeoOne, true>), (k_cg_a<R, GeoOne, false>), dim3(lc.ncg), dim3(kBlock), 0, s,
+                           ka, lc.cg, v, phik, cf);
+        c->next_nparts = lc.cg.bpr;
+    }
+    LAUNCHCHK();
+    return HMC_OK;
+}
+
 // One status chunk: `chunk` iterations (steps A and B, and the preconditioner passes), then
 // the reliable-update / true-residual sequence for units in `filter`, then what makes the
 // published records complete.  first: the first chunk of an unpreconditioned solve (its
@@ -1202,33 +1226,23 @@ static int enqueue_chunk(hmc_ctx* c, const Launch<Geo>& lc, int n, const double*
     const int grid = lc.ncg;
     int apart = chunk;    // iterations whose steps and passes are launches of their own
     if constexpr (std::is_same<Geo, GeoOne>::value) {
-        if (lc.joined()) {
+        if (lc.join_b) {      // with it step A, or not
             apart = 0;
             for (int i = 0; i < chunk; ++i) {
                 int rc = HMC_OK;
-                // the chunk's first step A finds z already transformed back
                 if (i > 0 && lc.join_a) {
                     rc = enqueue_joined<R>(c, lc, false, n, next_ctl(c, PEND_RZ), v, phik, cf, s);
                     if (rc) return rc;
                     c->next_nparts = c->Lt;
                 } else {
-                    launch_step_march<R, Geo>(c, lc, false, next_ctl(c, PEND_NONE), v, phik, cf, lc.cgm_per_unit * n,
-                                              lc.cgm_threads, lc.cgm_lds, nullptr, s);
-                    LAUNCHCHK();
-                    c->next_nparts = lc.cgm_per_unit;
-                }
-                if (lc.join_b) {
-                    rc = enqueue_joined<R>(c, lc, true, n, next_ctl(c, PEND_TT), v, phik, cf, s);
+                    // alone, or the chunk's first, which finds z already transformed back
+                    rc = enqueue_step_a<R>(c, lc, n, v, phik, cf, s);
                     if (rc) return rc;
-                    c->next_nparts = c->Lt;
-                } else {
-                    launch_step_march<R, Geo>(c, lc, true, next_ctl(c, PEND_TT), v, phik, cf, lc.cgm_per_unit * n,
-                                              lc.cgm_threads, lc.cgm_lds, nullptr, s);
-                    LAUNCHCHK();
-                    c->next_nparts = lc.cgm_per_unit;
                 }
-                rc = enqueue_pc<R, Geo>(c, lc, v, PEND_RR, s, nullptr, lc.join_b ? 1 : 0,
-                                        lc.join_a && i + 1 < chunk ? 1 : 2);
+                rc = enqueue_joined<R>(c, lc, true, n, next_ctl(c, PEND_TT), v, phik, cf, s);
+                if (rc) return rc;
+                c->next_nparts = c->Lt;
+                rc = enqueue_pc<R, Geo>(c, lc, v, PEND_RR, s, nullptr, 1, lc.join_a && i + 1 < chunk ? 1 : 2);
                 if (rc) return rc;
             }
         }
