@@ -2,6 +2,7 @@
 
 Usage: python -m paper_2204_14241_amd.build   (or build_library() from Python)
 """
+import glob
 import os
 import subprocess
 import sys
@@ -13,8 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhmc.so")
 SOURCES = [os.path.join(CSRC, f) for f in ("hmc.hip", "fft_f32.hip", "fft_f64.hip", "fft_metric.hip")]
-DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("kernels.h", "lattice.h", "fft.h", "fft_kernels.h", "precond.h", "metric.h",
-                                                  "probe.h", "march.h", "small.h")] + [
+DEPS = SOURCES + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [
     os.path.join(ROOT, "include", f) for f in ("hmc.h", "hmc_testing.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
