@@ -56,6 +56,14 @@ int hmc_test_precond(int L, int L_tau, double dtau, const hmc_params* params, co
  * the iteration cap if capped), with iters iterations done of maxit: 0 on, 3 done, 4 stopped, 5 failed. */
 int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit);
 
+/* The host loop of a solve that needs `need` iterations, on records that leave max(1, need - done + bias)
+ * iterations to do, after a solve of last_solve iterations (0: the context's first), in chunks of
+ * `chunk` iterations (shorter ones where free_len), the first k0 of them already run (fewer than the
+ * solve needs) and read.
+ * out[0]: chunks issued; out[1]: those of them that begin after the solve has ended; out[2]: times the
+ * host waited with nothing else in flight.  Returns 0, or -1 for a bad argument. */
+int hmc_test_chunks(int need, int bias, int last_solve, int chunk, int free_len, int k0, int out[3]);
+
 /* The kernels a solve of n right-hand sides would run with the context's present settings: the sum of
  * the values below (steps A and B joined with the preconditioner's slice passes, step A a march where it
  * stands alone), or -1 for a bad argument. */

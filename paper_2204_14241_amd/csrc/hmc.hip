@@ -1051,6 +1051,72 @@ static int iterations_left(const CgState& h) {
     return int(std::min(1e6, 1.0 + to_go * h.iters / fallen));
 }
 
+// How far the host issues a solve's status chunks ahead of its reads of their records: one chunk, so
+// that the GPU never idles on the host, except when the records (or, before the first ones, the last
+// solve) say that the chunk in flight should be the last.  A chunk past the end is some hundred
+// launches that do nothing, 2-5 us each, where waiting costs 30 us if the estimate was wrong.  With
+// free_len a chunk's length is free (nothing but the status check happens at its end): the last
+// one is cut to the estimate, and a context's first solve, of which nothing is known, goes ahead by
+// kShortChunk iterations only.
+constexpr int kShortChunk = 8;
+struct Lookahead {
+    int chunk;              // iterations of a chunk
+    bool free_len;
+    bool any = false;       // a chunk was issued
+    bool known = false;     // there is an estimate:
+    int left = 0;           // about how many iterations beyond the chunks issued
+    int length() const {
+        if (!free_len || (known && left <= 0) || !(known || any)) return chunk;
+        return known ? std::max(kShortChunk, std::min(chunk, left + 4)) : kShortChunk;
+    }
+    void issued(int len) {
+        any = true;
+        if (known) left -= len;
+    }
+    // Records that leave `est` iterations to do, `after` of them in a chunk issued since.
+    void read(int est, int after) {
+        known = true;
+        left = est - after;
+    }
+    bool wait() const { return known && left <= 0; }
+};
+
+// Chunks k0, k0 + 1, ... until the records read say that every unit is finished (all) or more than
+// `most` iterations are issued.  issue(k, len) enqueues a chunk and the copy of its records;
+// settle(k, est) waits for that copy, sets all and the iterations that still have to follow.  Returns an
+// error code; unread: a chunk is in flight whose records were not read.
+template <class Issue, class Settle>
+static int run_chunks(Lookahead& a, int k0, int last_solve, long long most, const Issue& issue, const Settle& settle,
+                      bool& all, bool& unread) {
+    long long total = (long long)k0 * a.chunk;
+    int est = 0;
+    unread = false;
+    for (int k = k0;; ++k) {
+        const int len = a.length();
+        int rc = issue(k, len);
+        if (rc) return rc;
+        a.issued(len);
+        total += len;
+        if (unread) {
+            rc = settle(k - 1, est);
+            if (rc || all) return rc;
+            a.read(est, len);
+        } else if (k == 0 && last_solve > 0) {
+            a.read(last_solve, len);
+        }
+        unread = true;
+        if (a.wait()) {
+            rc = settle(k, est);
+            if (rc) return rc;
+            unread = false;
+            if (all) return HMC_OK;
+            a.read(est, 0);
+        }
+        // the device enforces cg_maxit; this bound only guards the host loop
+        if (total > most) return HMC_OK;
+    }
+}
+
 static bool finished(int mode) { return mode == CG_DONE || mode == CG_STOPPED || mode == CG_FAILED; }
 
 // Control block for the next CG launch; advances the state-record parity.
@@ -1559,28 +1625,31 @@ static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64,
         for (int j = 0; j < n; ++j) done_early = done_early && finished(c->h_st[j].mode);
     }
 
-    int issued = k0 * chunk;
-    int k = k0;
-    bool have_prev = false;
     const int kt_a = mixed ? 0 : 2;
     const bool sample = c->timing && !use_graphs;
     bool start_active_prev = true;   // were all units iterating when chunk k-1 began
     bool all = false;                // the last records read: every unit is finished
-    int left = 0;                    // ... and about how many iterations the others still need
-    const CgState* last = c->h_st;   // ... where they are
+    bool unread = false;             // a chunk is in flight past them
+    const CgState* last = c->h_st;   // where they are
     int size[2] = {chunk, chunk};    // iterations of the last two chunks
+    // About how many iterations the unfinished units of the records still need.
+    auto iterations_to_go = [&](const CgState* hs) {
+        int left = 0;
+        for (int u = 0; u < n; ++u)
+            if (!finished(hs[u].mode)) left = std::max(left, iterations_left(hs[u]));
+        return left;
+    };
     // Wait for chunk j's records.
-    auto settle = [&](int j) -> int {
+    auto settle = [&](int j, int& est) -> int {
         HIPCHK(hipEventSynchronize(c->ev[j & 1]));
         const CgState* hs = last = c->h_st + size_t(j & 1) * c->nunits;
         bool all_active = true;
         all = true;
-        left = 0;
         for (int u = 0; u < n; ++u) {
             all = all && finished(hs[u].mode);
             all_active = all_active && hs[u].mode == CG_ACTIVE;
-            if (!finished(hs[u].mode)) left = std::max(left, iterations_left(hs[u]));
         }
+        est = iterations_to_go(hs);
         // chunk j began in the state chunk j-1 ended in; if every unit was iterating then and is
         // still iterating at its end, its mid-chunk sample did full work
         if (sample && start_active_prev && all_active) {
@@ -1602,16 +1671,7 @@ static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64,
         start_active_prev = all_active;
         return HMC_OK;
     };
-    // Chunks are issued one ahead of the status read, so the GPU never idles on the host, except
-    // when the records (or, before the first ones, the last solve) say that the chunk in flight
-    // should be the last: a chunk past the end is some hundred launches that do nothing, 2-5 us each,
-    // where waiting costs 30 us if the estimate was wrong.  In FP64 a chunk's length is free
-    // (nothing but the status check happens at its end): the last one is cut to the estimate.  Not
-    // where step A is joined: a chunk's first step A stands alone and sums |t|^2 in another order, so
-    // the chunks' lengths must not depend on earlier solves.
-    for (; !done_early;) {
-        int len = chunk;
-        if (!mixed && !use_graphs && !lc.join_a && left > 0) len = std::max(8, std::min(chunk, left + 4));
+    auto issue = [&](int k, int len) -> int {
         if (use_graphs) {
             HIPCHK(hipGraphLaunch(c->cgg[mixed ? 1 : 0].exec[k == 0 ? 0 : 1], s));
             c->seq += chunk_launches(chunk, lc.pc, lc.joined());
@@ -1620,33 +1680,24 @@ static int cg_run(hmc_ctx* c, const Launch<Geo>& lc, int n, const double* phi64,
             if (rc) return rc;
         }
         size[k & 1] = len;
-        issued += len;
         HIPCHK(hipMemcpyAsync(c->h_st + size_t(k & 1) * c->nunits, current_states(c), st_bytes,
                               hipMemcpyDeviceToHost, s));
         HIPCHK(hipEventRecord(c->ev[k & 1], s));
-        if (have_prev) {
-            int rc = settle(k - 1);
-            if (rc) return rc;
-            if (all) break;
-            left -= len;
-        } else if (k == k0) {
-            left = k == 0 && c->sg_last_iters > 0 ? c->sg_last_iters - len : 1;
-        }
-        have_prev = true;
-        if (left <= 0) {   // expected to end in this chunk
-            int rc = settle(k);
-            if (rc) return rc;
-            have_prev = false;
-            if (all) break;
-        }
-        ++k;
-        // the device enforces cg_maxit; this bound only guards the host loop
-        if (issued > c->p.cg_maxit + 4 * chunk) break;
+        return HMC_OK;
+    };
+    if (!done_early) {
+        // In FP64 a chunk's length is free, but not where step A is joined: a chunk's first step A
+        // stands alone and sums |t|^2 in another order, so the chunks' lengths must not depend on
+        // earlier solves.
+        Lookahead ahead{chunk, !mixed && !use_graphs && !lc.join_a};
+        if (k0 > 0) ahead.read(iterations_to_go(c->h_st), 0);     // the step graph's records
+        int rc = run_chunks(ahead, k0, c->sg_last_iters, c->p.cg_maxit + 4LL * chunk, issue, settle, all, unread);
+        if (rc) return rc;
     }
     if (!done_early) {
         if (all) {
             // finished records do not change; a chunk issued past them only has to drain
-            if (have_prev) HIPCHK(hipStreamSynchronize(s));
+            if (unread) HIPCHK(hipStreamSynchronize(s));
             if (last != c->h_st) std::memcpy(c->h_st, last, st_bytes);
         } else {
             HIPCHK(hipMemcpyAsync(c->h_st, current_states(c), st_bytes, hipMemcpyDeviceToHost, s));
@@ -2730,6 +2781,32 @@ int hmc_test_solve_path(const hmc_ctx* c, int n) {
                (l.cgm_per_unit > 0 ? HMC_TEST_PATH_MARCH : 0);
     };
     return c->p.precision == HMC_MIXED ? path(launch_one<float>(c, n), false) : path(launch_one<double>(c, n), true);
+}
+
+int hmc_test_chunks(int need, int bias, int last_solve, int chunk, int free_len, int k0, int out[3]) {
+    if (need < 1 || chunk < 1 || k0 < 0 || out == nullptr) return -1;
+    std::vector<int> done(size_t(k0), 0);        // iterations issued up to the end of each chunk
+    for (int k = 0; k < k0; ++k) done[size_t(k)] = (k + 1) * chunk;
+    auto to_go = [&](int did) { return std::max(1, need - did + bias); };
+    bool all = false, unread = false;
+    out[0] = out[1] = out[2] = 0;
+    auto issue = [&](int k, int len) {
+        const int before = k > 0 ? done[size_t(k - 1)] : 0;
+        if (before >= need) out[1] += 1;
+        out[0] += 1;
+        done.push_back(before + len);
+        return HMC_OK;
+    };
+    auto settle = [&](int k, int& est) {
+        if (size_t(k) + 1 == done.size()) out[2] += 1;
+        all = done[size_t(k)] >= need;
+        est = to_go(done[size_t(k)]);
+        return HMC_OK;
+    };
+    Lookahead a{chunk, free_len != 0};
+    if (k0 > 0) a.read(to_go(k0 * chunk), 0);
+    (void)run_chunks(a, k0, last_solve, 1LL << 30, issue, settle, all, unread);
+    return all ? 0 : -1;
 }
 
 int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit) {

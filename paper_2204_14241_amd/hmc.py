@@ -688,6 +688,14 @@ def test_fft_freq(n, pos):
     return _lib.load().hmc_test_fft_freq(n, pos)
 
 
+def test_chunks(need, bias=0, last_solve=0, chunk=32, free_len=False, k0=0):
+    """The host loop of a solve on simulated records: (chunks issued, those past the solve's end, waits
+    with nothing else in flight)."""
+    out = (ctypes.c_int * 3)()
+    rc = _lib.load().hmc_test_chunks(need, bias, last_solve, chunk, int(free_len), k0, out)
+    return None if rc else tuple(out)
+
+
 def test_small_next(rt, stop_rr, capped, iters, maxit):
     """Where the one-kernel solve goes after a true residual: 0 on, 3 done, 4 stopped, 5 failed."""
     return _lib.load().hmc_test_small_next(rt, stop_rr, int(capped), iters, maxit)
