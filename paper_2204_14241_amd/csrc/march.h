@@ -21,6 +21,8 @@
 // order.
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace hmc {
@@ -139,15 +141,44 @@ __device__ __forceinline__ void mdag_pair_lds(const float2* __restrict__ chi, in
 }
 
 // FP64 form of stencil_pair_lds at the site (x, y), phi(tau) there given as (q1, q2, q3) before
-// the coupling and the staggered sign are applied.
+// the coupling and the staggered sign are applied.  The rows' offsets are written out: through
+// stencil_site_at (the same operations) step B took 138 registers for 126, three wavefronts a SIMD
+// for four, and 56.9 us for 49.2 at 80 x 80 x 200.
 template <bool NN2 = false>
 __device__ __forceinline__ void stencil_site_lds(const double2* __restrict__ chi, int r, int x, int y, int L,
                                                  double f1, double f2, double f3, const Coef<double>& cf,
                                                  double ts, const double2 (&tt)[4], double2 (&o)[4],
                                                  double2 (&cen)[4]) {
     const int rowc = 4 * L;
-    stencil_site_at<double, NN2>([&](int d, int c, int yy) __attribute__((always_inline)) { return chi[(r + d) * rowc + c * L + yy]; },
-                                 x, y, L, f1, f2, f3, cf, ts, tt, o, cen);
+    const int yp = y + 1 == L ? 0 : y + 1, ym = y == 0 ? L - 1 : y - 1;
+    const int ypp = y + 2 >= L ? y + 2 - L : y + 2, ymm = y < 2 ? y - 2 + L : y - 2;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) cen[c] = chi[r * rowc + c * L + y];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int a = c >> 1;
+        const double2 hx = add<double>(chi[(r + 1) * rowc + c * L + y], chi[(r - 1) * rowc + c * L + y]);
+        const double2 hy = add<double>(chi[r * rowc + c * L + yp], chi[r * rowc + c * L + ym]);
+        double2 v = scl<double>(cf.diag[a], cen[c]);
+        v = axpy<double>(cf.hop[a][0], hx, v);
+        v = axpy<double>(cf.hop[a][1], hy, v);
+        v = axpy<double>(ts, tt[c], v);
+        if constexpr (NN2) {
+            v = axpy<double>(cf.hop2[a][0], add<double>(chi[(r + 2) * rowc + c * L + y], chi[(r - 2) * rowc + c * L + y]), v);
+            v = axpy<double>(cf.hop2[a][1], add<double>(chi[r * rowc + c * L + ypp], chi[r * rowc + c * L + ymm]), v);
+        }
+        o[c] = v;
+    }
+    const double g = cf.cpl * double(((x + y) & 1) ? -1 : 1);
+    const double q1 = g * f1, q2 = g * f2, q3 = g * f3;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const double2 u = cen[2 * (1 - a)], w = cen[2 * (1 - a) + 1];
+        o[2 * a].x += q3 * u.x + q1 * w.x + q2 * w.y;
+        o[2 * a].y += q3 * u.y + q1 * w.y - q2 * w.x;
+        o[2 * a + 1].x += q1 * u.x - q2 * u.y - q3 * w.x;
+        o[2 * a + 1].y += q1 * u.y + q2 * u.x - q3 * w.y;
+    }
 }
 
 __device__ __forceinline__ void mdag_site_lds(const double2* __restrict__ chi, int r, int x, int y, int s,
@@ -881,12 +912,14 @@ __global__ __launch_bounds__(kMarchCgThreads) void k_ru_apply_march(CgCtl ctl, M
 // (PEND_RU, one per workgroup) for the units in `filter`.  M^dagger needs t64(tau - 1) only at
 // the site itself: each slice's own element is kept in registers for the next.  LDS holds
 // t64(tau) on the band's rows and the rows beside it, alternating between two buffers so that
-// one barrier per slice suffices; the next slice's loads are in flight meanwhile.
+// one barrier per slice suffices; the next slice's loads are in flight meanwhile.  One lattice with
+// the nearest neighbours: four wavefronts per SIMD asked for (124 registers, no spill; the compiler
+// takes 129 by itself): 44.2 us at 80 x 80 x 200 against 49.3 with three.
 template <typename R, class MG, bool NN2>
-__global__ __launch_bounds__(kMarchCgThreads) void k_ru_resid_march(CgCtl ctl, MG mg, const double2* __restrict__ b,
-                                                                    const double2* __restrict__ t64,
-                                                                    const double* __restrict__ phi_base,
-                                                                    Coef<double> cf, C2<R>* __restrict__ r, int filter) {
+__global__ __launch_bounds__(kMarchCgThreads) __attribute__((
+    amdgpu_waves_per_eu(std::is_same<MG, MGeoOne>::value && !NN2 ? 4 : 1)))
+void k_ru_resid_march(CgCtl ctl, MG mg, const double2* __restrict__ b, const double2* __restrict__ t64,
+                      const double* __restrict__ phi_base, Coef<double> cf, C2<R>* __restrict__ r, int filter) {
     extern __shared__ __align__(16) unsigned char march_smem[];
     const MarchWork w = mg.at(xcd_remap(blockIdx.x, gridDim.x));
     const Lat& lat = w.lat;
