@@ -184,6 +184,7 @@ struct hmc_ctx {
     long long blob_doubles = 0;    // preconditioner tables of all lattices
     // an L (pc_wide) or an N_tau (mt_wide) needs an FFT radix above kFftNarrow
     bool pc_wide = false, mt_wide = false;
+    bool pc_lds_set[2] = {false, false};   // the preconditioner kernels may take their LDS [FP64, FP32]
     SliceCut mt_cut{};             // slice passes of the metric: one slice per workgroup
     // Fourier-diagonal HMC metric (one lattice): the caller's sigma table (null: identity,
     // plain drift and kinetic energy), whether this lattice supports the metric passes, their
@@ -1159,6 +1160,33 @@ static void launch_timed(void (*k)(P...), int grid, int block, size_t lds, hipSt
     else hipLaunchKernelGGL(k, dim3(grid), dim3(block), lds, s, static_cast<P>(a)...);
 }
 
+// Allow the slice passes and the joined steps their dynamic LDS (the tau pass stays below the 64 KB that
+// need no leave), before a context's first launch of them in precision R.  Not at its creation: a
+// context may never use them, and the attributes of all of them took 2-4 us of its 65.
+template <typename R, class Geo, int MAXR>
+static void pc_lds_attributes_r() {
+    const size_t xy = kPcLdsMost;
+    const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_xy<R, false, Geo, MAXR>), a, int(xy));
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_xy<R, true, Geo, MAXR>), a, int(xy));
+    if constexpr (std::is_same<Geo, GeoOne>::value) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_a<R, false, MAXR>), a, int(xy));
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_a<R, true, MAXR>), a, int(xy));
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_b<R, false, MAXR>), a, int(xy));
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_b<R, true, MAXR>), a, int(xy));
+    }
+    (void)hipGetLastError();
+}
+
+template <typename R, class Geo>
+static void pc_lds_attributes(hmc_ctx* c) {
+    const int pi = sizeof(R) == sizeof(float) ? 1 : 0;
+    if (c->pc_lds_set[pi]) return;
+    if (c->pc_wide) pc_lds_attributes_r<R, Geo, kFftMaxRadix>();
+    else pc_lds_attributes_r<R, Geo, kFftNarrow>();
+    c->pc_lds_set[pi] = true;
+}
+
 // The preconditioner passes, z = P r, for the units whose residual just changed; the first consumes
 // the pending kind `expect1` (a new |r|^2, the first |b|^2 or a true residual).  first, last: the
 // passes to run (0 forward, 1 tau, 2 inverse).
@@ -1790,6 +1818,7 @@ static int drift(hmc_ctx* c, double* phi, const double* pi, double eps, hipStrea
 template <typename R, class Geo>
 static int drift_solve(hmc_ctx* c, const Launch<Geo>& lc, int n, double* phi, const double* pi, double eps,
                        const double2* b, double2* x, hipStream_t s) {
+    if (lc.pc) pc_lds_attributes<R, Geo>(c);
     if constexpr (std::is_same<Geo, GeoOne>::value && sizeof(R) == sizeof(double)) {
         if (small_lattice(c, lc.pc)) {
             if (pi) {
@@ -2127,36 +2156,6 @@ static int check_precond(const hmc_ctx* c, const hmc_params* p) {
     return HMC_OK;
 }
 
-// Allow the preconditioner passes their dynamic LDS (above the default per-workgroup amount).
-template <typename R, class Geo, int MAXR>
-static void pc_lds_attributes_r(size_t t) {
-    const size_t xy = kPcLdsMost;
-    const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_xy<R, false, Geo, MAXR>), a, int(xy));
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_xy<R, true, Geo, MAXR>), a, int(xy));
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_t<R, Geo, false>), a, int(t));
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_t<R, Geo, true>), a, int(t));
-    if constexpr (std::is_same<Geo, GeoOne>::value) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_a<R, false, MAXR>), a, int(xy));
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_a<R, true, MAXR>), a, int(xy));
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_b<R, false, MAXR>), a, int(xy));
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pc_b<R, true, MAXR>), a, int(xy));
-    }
-}
-
-template <class Geo>
-static void pc_lds_attributes(const hmc_ctx* c) {
-    if (c->pc_ok[0]) {
-        if (c->pc_wide) pc_lds_attributes_r<double, Geo, kFftMaxRadix>(c->lds_t[0]);
-        else pc_lds_attributes_r<double, Geo, kFftNarrow>(c->lds_t[0]);
-    }
-    if (c->pc_ok[1]) {
-        if (c->pc_wide) pc_lds_attributes_r<float, Geo, kFftMaxRadix>(c->lds_t[1]);
-        else pc_lds_attributes_r<float, Geo, kFftNarrow>(c->lds_t[1]);
-    }
-    (void)hipGetLastError();
-}
-
 // Preconditioner tables of every lattice into the workspace; batch: the pass block tables.
 static int upload_pc(hmc_ctx* c) {
     std::vector<Lat> lats;
@@ -2193,9 +2192,7 @@ static int upload_pc(hmc_ctx* c) {
             HIPCHK(hipMemcpy(b.pxy_blocks[pi], xy[pi].data(), sizeof(int2) * xy[pi].size(), hipMemcpyHostToDevice));
         for (int pi = 0; pi < 2; ++pi)
             HIPCHK(hipMemcpy(b.pt_blocks[pi], t[pi].data(), sizeof(int2) * t[pi].size(), hipMemcpyHostToDevice));
-        pc_lds_attributes<GeoBatch>(c);
     } else {
-        pc_lds_attributes<GeoOne>(c);
         if (c->metric_ok) {
             const size_t mt_lds = mt_xy_lds(c->L, c->mt_cut.pitch);
             const hipFuncAttribute a = hipFuncAttributeMaxDynamicSharedMemorySize;
@@ -2704,6 +2701,7 @@ template <typename R>
 static int apply_precond_impl(hmc_ctx* c, const double2* in, void* out, int n, double* rz, hipStream_t s) {
     Launch<GeoOne> lc = launch_one<R>(c, n);
     lc.pc = true;
+    pc_lds_attributes<R, GeoOne>(c);
     CgVecs<R> v = KrylovBufs<R>::get(c, c->xsol, true);
     const size_t bytes = size_t(n) * 4 * size_t(c->vol) * sizeof(C2<R>);
     HIPCHK(hipMemsetAsync(v.z, 0, bytes, s));   // P 0 = 0: a zero input leaves z untouched
