@@ -259,6 +259,13 @@ __host__ __device__ __forceinline__ void order_pin(R& a, R& b) {
 #endif
 }
 
+// The lane's number, computed where it is used: one that is kept costs the tau pass a register.
+__device__ __forceinline__ int fresh_lane() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
 // Both recurrences on one thread's chunk (n values from tau = sp.t0), with the workgroup's map
 // exchange in LDS (a, c, x: Q x 64 entries, x one row more).  z comes out scaled by `scale`.
 // Returns sum |y|^2 over the chunk (y = K^{-1} r).  Between the barriers: the maps are written
@@ -267,7 +274,7 @@ __host__ __device__ __forceinline__ void order_pin(R& a, R& b) {
 // wave reaches after its reads.
 template <typename R, int MC, class N>
 __device__ __forceinline__ double pc_tau_solve(C2<R> (&v)[MC], N n, ChunkSpan sp, int Lt, R b, R scale, R* sa,
-                                               C2<R>* sc, C2<R>* sx, int q, int lane, int Q) {
+                                               C2<R>* sc, C2<R>* sx, int q, int Q) {
     const RecCoef<R> k = rec_coef(b);
     const bool wk = sp.n > 0 && sp.t0 + sp.n == Lt;   // holds tau = N_tau - 1 (K's wrap)
     const bool wkd = sp.n > 0 && sp.t0 == 0;          // holds tau = 0 (K^dagger's wrap)
@@ -277,11 +284,16 @@ __device__ __forceinline__ double pc_tau_solve(C2<R> (&v)[MC], N n, ChunkSpan sp
     chunk_scale<R, MC>(v, k.B);
     chunk_map<R, MC, true>(v, n, k, a, c);
     wrap_map<R>(wk, k.before, a, c);
+    int lane = fresh_lane();
     sa[q * kPcCols + lane] = a;
     sc[q * kPcCols + lane] = c;
     __syncthreads();
-    if (q == 0) chunk_close<R>(sa + lane, sc + lane, sx + lane, Q, kPcCols, k.before);
+    if (q == 0) {
+        lane = fresh_lane();
+        chunk_close<R>(sa + lane, sc + lane, sx + lane, Q, kPcCols, k.before);
+    }
     __syncthreads();
+    lane = fresh_lane();
     const C2<R> x1 = wrap_entry<R>(wk, k.before, sx[(k.before ? q : q + 1) * kPcCols + lane]);
     chunk_apply<R, MC, true>(v, n, k, x1);
     // then z = K^{-dagger} y, scaled: the registers walked down.  The norm is taken before the
@@ -292,11 +304,16 @@ __device__ __forceinline__ double pc_tau_solve(C2<R> (&v)[MC], N n, ChunkSpan sp
     chunk_scale<R, MC>(v, B2);
     chunk_map<R, MC, false>(v, n, k, a, c);
     wrap_map<R>(wkd, k.before, a, c);
+    lane = fresh_lane();
     sa[q * kPcCols + lane] = a;
     sc[q * kPcCols + lane] = c;
     __syncthreads();
-    if (q == 0) chunk_close<R>(sa + lane, sc + lane, sx + lane, Q, kPcCols, !k.before);
+    if (q == 0) {
+        lane = fresh_lane();
+        chunk_close<R>(sa + lane, sc + lane, sx + lane, Q, kPcCols, !k.before);
+    }
     __syncthreads();
+    lane = fresh_lane();
     const C2<R> x2 = wrap_entry<R>(wkd, k.before, sx[(k.before ? q + 1 : q) * kPcCols + lane]);
     chunk_apply<R, MC, false>(v, n, k, x2);
     return double(nrm);
@@ -308,8 +325,10 @@ __host__ __device__ inline size_t pc_tau_lds(int Q) {
     return size_t(Q) * kPcCols * (sizeof(R) + sizeof(C2<R>)) + size_t(Q + 1) * kPcCols * sizeof(C2<R>);
 }
 
-// Pass 2 (FP32: six waves per SIMD asked for, 80 registers, so that two 640-thread workgroups share
-// a CU: 20.4 us at 80 x 80 x 200 against 26.8 us with the 86 the compiler takes by itself): one
+// Pass 2 (FP32: six waves per SIMD, that is at most 80 registers, so that two 640-thread workgroups
+// share a CU: 19.7 us at 80 x 80 x 200 against 26.8 us with 86.  Lane numbers are computed where they are
+// used and the stores' addresses after the solve; kept through it, two or three of them go to scratch
+// memory at 80 registers: 21.2 us): one
 // workgroup per (component, group of 64 columns) of a unit, 64 Q threads (lane:
 // column, wavefront: chunk), Q = blockDim / 64 at least each lattice's pc_chunks.  FULL: every
 // lattice of the launch has N_tau = Q pc_chunk_max, so every chunk is full.
@@ -359,7 +378,7 @@ void k_pc_t(CgCtl ctl, Geo geo, C2<R>* z,
     const unsigned o0 = unsigned(on ? col : LL - 1) * unsigned(sizeof(C2<R>)) +
                         (rev && n > 0 ? unsigned(int(n) - 1) * unsigned(rowb) : 0u);
     int ob = rev ? -rowb : rowb;
-    auto at = [&](int j) { return reinterpret_cast<C2<R>*>(const_cast<char*>(zb) + (o0 + unsigned(j * ob))); };
+    auto at = [&](int j) { return reinterpret_cast<const C2<R>*>(zb + (o0 + unsigned(j * ob))); };
     // Registers j and MC - 1 - j are loaded and stored back to back: in a full chunk they cover
     // the same two rows between the forward and the reversed lanes, so each pair writes whole
     // cache lines while they are still in L2.
@@ -369,20 +388,32 @@ void k_pc_t(CgCtl ctl, Geo geo, C2<R>* z,
         const int j = (i & 1) ? MC - 1 - (i >> 1) : (i >> 1);
         v[j] = j < n ? *at(j) : mk<R>(R(0), R(0));
     }
-    // the stores recompute their addresses rather than keep the loads' live through the solve
-    asm volatile("" : "+v"(ob));
+    asm volatile("" : "+v"(ob));    // the stores' addresses are not the loads' kept
     R* sa = reinterpret_cast<R*>(pc_smem);
     C2<R>* sc = reinterpret_cast<C2<R>*>(sa + Q * kPcCols);
     C2<R>* sx = sc + Q * kPcCols;
     // z is stored with the inverse transform's 1 / L^2
-    const double pl = pc_tau_solve<R, MC>(v, n, sp, Lt, b, R(1) / R(LL), sa, sc, sx, q, lane, Q);
-    const double part = on ? pl : 0.0;
+    const double pl = pc_tau_solve<R, MC>(v, n, sp, Lt, b, R(1) / R(LL), sa, sc, sx, q, Q);
+    const int slane = fresh_lane(), scol = grp * kPcCols + slane;
+    const bool son = scol < LL;
+    const double part = son ? pl : 0.0;
+    const unsigned so = unsigned(son ? scol : LL - 1) * unsigned(sizeof(C2<R>)) +
+                        (ob < 0 && n > 0 ? unsigned(int(n) - 1) * unsigned(rowb) : 0u);
 #pragma unroll
     for (int i = 0; i < MC; ++i) {
         const int j = (i & 1) ? MC - 1 - (i >> 1) : (i >> 1);
-        if (j < n && on) *at(j) = v[j];
+        if (j < n && son) *reinterpret_cast<C2<R>*>(const_cast<char*>(zb) + (so + unsigned(j * ob))) = v[j];
     }
-    store_partial(ctl, PEND_RZ, pos, part / double(LL));
+    // store_partial by this kernel's own lane and wavefront numbers
+    __shared__ double red[pc_max_chunks<R>()];
+    const double sum = wave_sum(part / double(LL));
+    if (slane == 0) red[q] = sum;
+    __syncthreads();
+    if (q == 0 && slane == 0) {
+        double a = 0.0;
+        for (int i = 0; i < Q; ++i) a += red[i];
+        part_slot(ctl, PEND_RZ, pos)[pos.blk] = a;
+    }
 }
 
 }  // namespace hmc

@@ -1,6 +1,6 @@
 """Registers of the marches that are measured with a given number of wavefronts per SIMD, from the metadata
-of the library built here: 512 vector registers a SIMD lane, so four wavefronts with at most 128 each, and
-none of them in scratch memory."""
+of the library built here: 512 vector registers a SIMD lane, so four wavefronts with at most 128 each, six
+with at most 80, and none of them in scratch memory."""
 import os
 import re
 import struct
@@ -65,4 +65,12 @@ def found():
 def test_four_wavefronts_a_simd(found, kernel):
     k = found["void hmc::" + kernel]
     assert k[".vgpr_count"] <= 128
+    assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0
+
+
+@pytest.mark.parametrize("geo", ["GeoOne", "GeoBatch"])
+@pytest.mark.parametrize("full", ["true", "false"])
+def test_six_wavefronts_a_simd(found, geo, full):
+    k = found[f"void hmc::k_pc_t<float, hmc::{geo}, {full}>"]
+    assert k[".vgpr_count"] <= 80
     assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0
