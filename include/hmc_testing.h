@@ -56,6 +56,10 @@ int hmc_test_precond(int L, int L_tau, double dtau, const hmc_params* params, co
  * the iteration cap if capped), with iters iterations done of maxit: 0 on, 3 done, 4 stopped, 5 failed. */
 int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit);
 
+/* The march cut (rows, slices) that a solve of n right-hand sides takes by itself on one lattice, in
+ * precision HMC_FP64 or HMC_MIXED, with the two-site hops if nn2.  Returns 0, or -1 for a bad argument. */
+int hmc_test_auto_cut(int L, int L_tau, int n, int precision, int nn2, int out[2]);
+
 /* The host loop of a solve that needs `need` iterations, on records that leave max(1, need - done + bias)
  * iterations to do, after a solve of last_solve iterations (0: the context's first), in chunks of
  * `chunk` iterations (shorter ones where free_len), the first k0 of them already run (fewer than the

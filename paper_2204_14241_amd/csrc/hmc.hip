@@ -851,35 +851,53 @@ struct Launch {
 // band and slices per segment with the least estimated time of steps A and B.  A march of s slices
 // takes its launch, s + 1 dependent steps per round of workgroups, the memory traffic (with the
 // rows beside each band and the slice after each segment) and, when the workgroups do not divide
-// evenly over the CUs, the traffic of the busiest CU.  The coefficients (us, MB) are a fit to 1,500
-// cuts of 22 lattices from 8 x 8 x 16 to 80 x 80 x 200 with 1, 2 and 4 right-hand sides, where its choice
-// takes 1.02x the best cut's time on average (at worst 1.1x FP32, 1.3x FP64).  kDefaultRows x 8
-// slices, right where the lattice fills the chip, stays unless the estimate is a tenth below it: at 80 x 80 x 200
-// both ways take 69 us (FP32) and 138 us (FP64), while 20 x 20 x 100 goes from 29.8 to 12.7 us, 40 x 40 x 100 from
-// 33.2 to 16.1, and in FP64 40 x 40 x 100 with two right-hand sides from 48.0 to 38.0, 60 x 60 x 160 from
-// 74.0 to 60.2 us per iteration: eight slices in sequence on a few workgroups left most CUs idle.
+// evenly over the CUs, the traffic of the busiest CU.  A round is what the CU's SIMDs hold: a workgroup of
+// five to eight wavefronts takes two slots of a SIMD, so that only one such workgroup is resident where a
+// SIMD has three (FP32, two-site hops, 36 x 36 x 50 with sixteen vectors: 12 rows by 6 slices, five
+// wavefronts, 74 us an iteration, 8 by 6, four wavefronts, 63).  The coefficients rank cuts rather than give
+// times; they are fits to 12,000 cuts of 54 lattices and counts of vectors from 8 x 8 x 32 to 80 x 80 x 200 and
+// 1 to 16, with and without the two-site hops, where the choice takes 1.01x the fastest cut's time on
+// average and at worst 1.1x (FP64 without the hops 1.03x and 1.3x).  Over 580 others it is 1.25x to 1.64x
+// faster than kDefaultRows x kDefaultSlices on average and at worst 3% slower.  That cut, right where the
+// lattice fills the chip, stays unless the estimate is clearly below its own: at 80 x 80 x 200 both ways take
+// 69 us (FP32) and 138 us (FP64), while 20 x 20 x 100 goes from 29.8 to 12.7 us, 40 x 40 x 100 from 33.2 to
+// 16.1, and in FP64 40 x 40 x 100 with two right-hand sides from 48.0 to 38.0, 60 x 60 x 160 from 74.0 to 60.2 us
+// per iteration: eight slices in sequence on a few workgroups left most CUs idle.
 constexpr int kDefaultRows[2] = {4, 8};   // [FP64, FP32]
 constexpr int kDefaultSlices = 8;
+struct CutFit {
+    double k[5];     // the estimate's coefficients
+    int simd[2];     // wavefronts of steps A and B that a SIMD holds; 0: counted per CU, twelve of them
+    double keep;     // the default cut stays unless the estimate is below this part of its own
+};
+static const CutFit kCutFit[2][2] = {   // [FP64, FP32][nearest neighbours, two-site hops]
+    {{{8.0, 1.3, 0.063, 0.025, 0.41}, {0, 0}, 0.9}, {{12.9, 1.51, 0.0512, 0.0516, 0.77}, {2, 3}, 0.95}},
+    {{{8.78, 1.60, 0.0752, 0.0256, 0.0}, {3, 4}, 0.9}, {{11.0, 3.28, 0.070, 0.042, 0.168}, {3, 3}, 0.95}}};
 static Cut auto_cut(int L, int Lt, int n, int pi, int H, int slots) {
-    static const double coef[2][5] = {{8.0, 1.3, 0.063, 0.025, 0.41}, {7.4, 1.8, 0.064, 0.026, 0.26}};
     static const int segs[] = {1, 2, 3, 4, 6, 8, 10, 12};
-    const double* k = coef[pi];
+    const CutFit& f = kCutFit[pi][H - 1];
     const int per_row = pi ? L / 2 : L;
     const int top = std::min(L, kMarchCgThreads / per_row - 2 * H);
     auto estimate = [&](int R, int s) {
         const MarchPlan mp = make_march_plan(L, Lt, R, s);
         const long long wgs = (long long)mp.nband * mp.nseg * n;
-        const int waves = ((mp.R + 2 * H) * per_row + 63) / 64, resident = std::max(1, 12 / waves);
-        const long long busy = (wgs + 255) / 256, rounds = (busy + resident - 1) / resident;
+        const int waves = ((mp.R + 2 * H) * per_row + 63) / 64;
+        const long long busy = (wgs + 255) / 256;
+        double rounds = 0.0;    // of steps A and B on average
+        for (int per : f.simd) {
+            const int fit = per == 0 ? 12 / waves : waves < 4 ? 4 * per / waves : per / ((waves + 3) / 4);
+            const int resident = std::max(1, fit);
+            rounds += 0.5 * double((busy + resident - 1) / resident);
+        }
         // bytes per site: r (z), p and t with the rows beside the band and the next slice, the
         // stores, phi and every second iteration's solution update
         const double reals = 24.0 * (mp.R + 2 * H) / mp.R + 24.0 / mp.seglen + 50.0, mb = reals * (pi ? 4 : 8) * 1e-6;
-        return k[0] + k[1] * double(rounds * (mp.seglen + 1)) + k[2] * mb * L * L * Lt * n +
-               k[3] * mb * 256.0 * double(busy * mp.seglen) * mp.R * L + k[4] * double(wgs) / 256.0;
+        return f.k[0] + f.k[1] * rounds * (mp.seglen + 1) + f.k[2] * mb * L * L * Lt * n +
+               f.k[3] * mb * 256.0 * double(busy * mp.seglen) * mp.R * L + f.k[4] * double(wgs) / 256.0;
     };
     const Cut dflt{std::max(1, std::min(kDefaultRows[pi], top)), kDefaultSlices};
     Cut best = dflt;
-    double least = 0.9 * estimate(dflt.rows, dflt.slices);
+    double least = f.keep * estimate(dflt.rows, dflt.slices);
     for (int R = 1; R <= top; ++R)
         for (int s : segs) {
             const MarchPlan mp = make_march_plan(L, Lt, R, s);
@@ -2783,6 +2801,14 @@ int hmc_test_solve_path(const hmc_ctx* c, int n) {
                (l.cgm_per_unit > 0 ? HMC_TEST_PATH_MARCH : 0);
     };
     return c->p.precision == HMC_MIXED ? path(launch_one<float>(c, n), false) : path(launch_one<double>(c, n), true);
+}
+
+int hmc_test_auto_cut(int L, int Lt, int n, int precision, int nn2, int out[2]) {
+    if (!geometry_ok(L, Lt) || n < 1 || n > HMC_MAX_RHS || out == nullptr) return -1;
+    const Cut c = auto_cut(L, Lt, n, precision == HMC_MIXED ? 1 : 0, nn2 ? 2 : 1, unit_slots(make_lat(L, Lt)));
+    out[0] = c.rows;
+    out[1] = c.slices;
+    return 0;
 }
 
 int hmc_test_chunks(int need, int bias, int last_solve, int chunk, int free_len, int k0, int out[3]) {

@@ -688,6 +688,13 @@ def test_fft_freq(n, pos):
     return _lib.load().hmc_test_fft_freq(n, pos)
 
 
+def test_auto_cut(L, Lt, n, precision="fp64", nn2=False):
+    """(rows, slices) of the march cut a solve of n right-hand sides takes by itself (no GPU needed)."""
+    out = (ctypes.c_int * 2)()
+    rc = _lib.load().hmc_test_auto_cut(L, Lt, n, {"fp64": HMC_FP64, "mixed": HMC_MIXED}[precision], int(nn2), out)
+    return None if rc else tuple(out)
+
+
 def test_chunks(need, bias=0, last_solve=0, chunk=32, free_len=False, k0=0):
     """The host loop of a solve on simulated records: (chunks issued, those past the solve's end, waits
     with nothing else in flight)."""
