@@ -398,9 +398,12 @@ int hmc_get_mdm_shape(const hmc_ctx* ctx, int precision, int n, int* rows, int* 
  * ones), or the autotuner's choice.  FP64 solves without preconditioner on at most 512 sites run as
  * one kernel instead, and preconditioned solves on small lattices run steps A and B joined with the
  * preconditioner's slice passes (three launches an iteration), until a launch shape is set here, with
- * hmc_set_cg_march_step_b or with hmc_set_cg_workgroups, and while kernel times are sampled.  precision:
- * HMC_FP64, HMC_MIXED or -1 for both.  The algebra is that of the tile kernels; only the order
- * of the FP64 partial sums differs.  One-lattice contexts only (HMC_ERR_INVALID_ARG on a
+ * hmc_set_cg_march_step_b or with hmc_set_cg_workgroups, except while kernel times are sampled.  The
+ * algebra is that of the tile kernels; only the order of the FP64 partial sums differs.  A solve
+ * repeated with the same arguments and settings therefore gives the same bits; a vector solved with
+ * another number of right-hand sides, with kernel times sampled or at another launch shape meets the same
+ * true residual, but its last bits, and with them its iteration count by one, may differ.
+ * precision: HMC_FP64, HMC_MIXED or -1 for both.  One-lattice contexts only (HMC_ERR_INVALID_ARG on a
  * batch: hmc_batch_set_cg_march); lattices whose band does not fit (rows + 2 rows, or rows + 4
  * with the two-site hops, of one thread per element in FP64 or per pair in FP32, at most 512
  * threads) keep the tile kernels.  The FP64 setting also cuts the reliable update's FP64
