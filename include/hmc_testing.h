@@ -56,6 +56,11 @@ int hmc_test_precond(int L, int L_tau, double dtau, const hmc_params* params, co
  * the iteration cap if capped), with iters iterations done of maxit: 0 on, 3 done, 4 stopped, 5 failed. */
 int hmc_test_small_next(double rt, double stop_rr, int capped, int iters, int maxit);
 
+/* The block table of a batch launch: unit u (right-hand side u % nrhs of lattice u / nrhs, which has
+ * vols[u / nrhs] sites) runs counts[u] workgroups; out receives (unit, workgroup) pairs in the order
+ * in which the kernels read the table.  Returns their count, or -1 for a bad argument. */
+int hmc_test_spread_units(int nunits, int nrhs, const int* vols, const int* counts, int* out);
+
 /* The march cut (rows, slices) that a solve of n right-hand sides takes by itself on one lattice, in
  * precision HMC_FP64 or HMC_MIXED, with the two-site hops if nn2.  Returns 0, or -1 for a bad argument. */
 int hmc_test_auto_cut(int L, int L_tau, int n, int precision, int nn2, int out[2]);

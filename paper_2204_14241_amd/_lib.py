@@ -34,7 +34,7 @@ EXPORTED = [
     "hmc_apply_MdagM_f32", "hmc_apply_MdagM_noalloc", "hmc_cg_solve", "hmc_heatbath", "hmc_force",
     "hmc_force_from_solution", "hmc_pf_action", "hmc_boson_action", "hmc_trajectory",
     "hmc_strerror", "hmc_last_error", "hmc_test_site", "hmc_test_xcd_remap", "hmc_test_tile_span", "hmc_test_fft",
-    "hmc_test_fft_freq", "hmc_test_auto_cut", "hmc_test_chunks", "hmc_test_small_next", "hmc_test_solve_path", "hmc_test_precond", "hmc_test_apply_precond", "hmc_stream_probe",
+    "hmc_test_fft_freq", "hmc_test_spread_units", "hmc_test_auto_cut", "hmc_test_chunks", "hmc_test_small_next", "hmc_test_solve_path", "hmc_test_precond", "hmc_test_apply_precond", "hmc_stream_probe",
     "hmc_set_kernel_timing", "hmc_get_kernel_times", "hmc_set_cg_workgroups",
     "hmc_get_cg_workgroups", "hmc_set_mdm_shape", "hmc_get_mdm_shape", "hmc_set_cg_march", "hmc_get_cg_march", "hmc_set_cg_march_step_b", "hmc_get_cg_march_step_b", "hmc_leapfrog", "hmc_autotune", "hmc_set_graphs", "hmc_set_step_graphs",
     "hmc_set_metric", "hmc_metric_momenta", "hmc_metric_kinetic", "hmc_metric_norm2",
@@ -200,6 +200,7 @@ def load():
         "hmc_test_tile_span": (I, [I, I, I, ctypes.POINTER(ctypes.c_int)]),
         "hmc_test_fft": (I, [I, I, ctypes.POINTER(D), ctypes.POINTER(D)]),
         "hmc_test_fft_freq": (I, [I, I]),
+        "hmc_test_spread_units": (I, [I, I, ctypes.POINTER(I), ctypes.POINTER(I), ctypes.POINTER(I)]),
         "hmc_test_auto_cut": (I, [I, I, I, I, I, ctypes.POINTER(I)]),
         "hmc_test_chunks": (I, [I, I, I, I, I, I, ctypes.POINTER(I)]),
         "hmc_test_small_next": (I, [D, D, I, I, I]),

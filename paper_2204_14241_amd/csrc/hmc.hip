@@ -2803,6 +2803,21 @@ int hmc_test_solve_path(const hmc_ctx* c, int n) {
     return c->p.precision == HMC_MIXED ? path(launch_one<float>(c, n), false) : path(launch_one<double>(c, n), true);
 }
 
+int hmc_test_spread_units(int nunits, int nrhs, const int* vols, const int* counts, int* out) {
+    if (nunits < 1 || nrhs < 1 || nunits % nrhs != 0 || vols == nullptr || counts == nullptr || out == nullptr) return -1;
+    std::vector<Lat> lats(size_t(nunits / nrhs));
+    for (size_t i = 0; i < lats.size(); ++i) lats[i].vol = vols[i];
+    std::vector<int2> by_unit;
+    for (int u = 0; u < nunits; ++u)
+        for (int w = 0; w < counts[u]; ++w) by_unit.push_back(make_int2(u, w));
+    const std::vector<int2> all = spread_units(by_unit, lats, nrhs);
+    for (size_t i = 0; i < all.size(); ++i) {
+        out[2 * i] = all[i].x;
+        out[2 * i + 1] = all[i].y;
+    }
+    return int(all.size());
+}
+
 int hmc_test_auto_cut(int L, int Lt, int n, int precision, int nn2, int out[2]) {
     if (!geometry_ok(L, Lt) || n < 1 || n > HMC_MAX_RHS || out == nullptr) return -1;
     const Cut c = auto_cut(L, Lt, n, precision == HMC_MIXED ? 1 : 0, nn2 ? 2 : 1, unit_slots(make_lat(L, Lt)));

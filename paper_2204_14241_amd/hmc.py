@@ -688,6 +688,14 @@ def test_fft_freq(n, pos):
     return _lib.load().hmc_test_fft_freq(n, pos)
 
 
+def test_spread_units(vols, counts, nrhs=1):
+    """The (unit, workgroup) pairs of a batch launch in table order: counts per unit, vols per lattice."""
+    n = len(counts)
+    out = (ctypes.c_int * max(1, 2 * sum(counts)))()
+    m = _lib.load().hmc_test_spread_units(n, nrhs, (ctypes.c_int * len(vols))(*vols), (ctypes.c_int * n)(*counts), out)
+    return None if m < 0 else [(out[2 * i], out[2 * i + 1]) for i in range(m)]
+
+
 def test_auto_cut(L, Lt, n, precision="fp64", nn2=False):
     """(rows, slices) of the march cut a solve of n right-hand sides takes by itself (no GPU needed)."""
     out = (ctypes.c_int * 2)()
