@@ -2555,7 +2555,8 @@ static int apply_impl(hmc_ctx* c, const R* phi, const void* in, void* out, int n
 // workgroups (a segment forms three slices before its first result), the traffic, and the busiest
 // CU's.  us, with 8 (FP32) or 4 (FP64) rows and 8 slices -> chosen: 12 x 12 x 40 FP64 12.9 -> 7.4 (what the call costs),
 // 40 x 40 x 100 FP64 16.2 -> 9.8, 60 x 60 x 160 FP64 37.2 -> 23.3, 80 x 80 x 40 FP32 19.8 -> 9.4, 80 x 80 x 200 FP32 two
-// vectors 50.0 -> 44.6; 80 x 80 x 200 with one vector keeps its cut (24.7 FP32, 50.5 FP64).
+// vectors 50.0 -> 44.6.  80 x 80 x 200 with one vector takes 12 rows by 6 slices in FP32 (22.9 -> 21.7 on the
+// same vector again, level at 27.4 on new ones) and keeps its cut in FP64 (42.8, new vectors 50.8).
 static Cut auto_mdm(int L, int Lt, int n, int pi) {
     static const double coef[2][4] = {{2.06, 0.795, 0.0008, 0.0531}, {0.74, 1.19, 0.0019, 0.0426}};
     static const int segs[] = {2, 3, 4, 6, 8, 12};
