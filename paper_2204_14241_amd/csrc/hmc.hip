@@ -616,6 +616,7 @@ static std::vector<int2> spread_units(const std::vector<int2>& by_unit, const st
         return lats[size_t(by_unit[a.first].x / nrhs)].vol > lats[size_t(by_unit[b.first].x / nrhs)].vol;
     });
     std::vector<int2> of[kNumXcd];
+    for (auto& o : of) o.reserve(by_unit.size() / kNumXcd + runs.size());
     size_t turn = 0;      // the XCD that takes the next workgroup beyond a unit's equal shares
     for (const auto& r : runs) {
         const size_t n = r.second - r.first, share = n / kNumXcd, over = n % kNumXcd;
@@ -628,6 +629,7 @@ static std::vector<int2> spread_units(const std::vector<int2>& by_unit, const st
         turn = (turn + over) % kNumXcd;
     }
     std::vector<int2> out;
+    out.reserve(by_unit.size());
     for (const auto& o : of) out.insert(out.end(), o.begin(), o.end());
     return out;
 }
@@ -643,6 +645,12 @@ static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
     b.mlds[pi] = b.rlds[pi] = 0;
     int part = 0;
     const int seg = batch_slices(c, pi), rseg = batch_slices(c, 0);
+    const bool tables = c->ws != nullptr;    // counts only until the workspace is set
+    int nb = 0, nm = 0, nr = 0;
+    auto list = [&](std::vector<int2>& v, int& n, int u, int workgroups) {
+        n += workgroups;
+        for (int w = 0; tables && w < workgroups; ++w) v.push_back(make_int2(u, w));
+    };
     for (int ch = 0; ch < b.nchains; ++ch) {
         const Lat& lat = b.lats[size_t(ch)];
         for (int k = 0; k < b.nrhs; ++k) {
@@ -657,30 +665,30 @@ static int upload_batch_shape(hmc_ctx* c, int pi, int max_bpr) {
             d.chain = ch;
             d.pcoff = int(b.pcoff[size_t(ch)]);
             d.sc = pi ? slice_cut<float>(lat.L, kAllSlices) : slice_cut<double>(lat.L, kAllSlices);
-            for (int w = 0; w < d.bpr; ++w) blocks.push_back(make_int2(u, w));
+            list(blocks, nb, u, d.bpr);
             int th = 0;
             size_t lds = 0;
             d.mp = batch_march_plan(lat, c->cgm_rows[pi], seg, pi == 1, unit_slots(lat), d.mparts, th, lds);
             m_ok = m_ok && d.mparts > 0;
             b.mthreads[pi] = std::max(b.mthreads[pi], th);
             b.mlds[pi] = std::max(b.mlds[pi], lds);
-            for (int w = 0; w < d.mparts; ++w) mblocks.push_back(make_int2(u, w));
+            list(mblocks, nm, u, d.mparts);
             d.rmp = batch_march_plan(lat, c->cgm_rows[0], rseg, false, unit_slots(lat), d.rparts, th, lds);
             r_ok = r_ok && d.rparts > 0;
             b.rthreads[pi] = std::max(b.rthreads[pi], th);
             b.rlds[pi] = std::max(b.rlds[pi], lds);
-            for (int w = 0; w < d.rparts; ++w) rblocks.push_back(make_int2(u, w));
+            list(rblocks, nr, u, d.rparts);
         }
     }
-    blocks = spread_units(blocks, b.lats, b.nrhs);
-    mblocks = spread_units(mblocks, b.lats, b.nrhs);
-    rblocks = spread_units(rblocks, b.lats, b.nrhs);
-    b.nblocks[pi] = int(blocks.size());
+    b.nblocks[pi] = nb;
     // a launch marches every unit or none
-    b.mgrid[pi] = m_ok ? int(mblocks.size()) : 0;
-    b.rgrid[pi] = r_ok ? int(rblocks.size()) : 0;
+    b.mgrid[pi] = m_ok ? nm : 0;
+    b.rgrid[pi] = r_ok ? nr : 0;
     b.hunits[pi] = units;
-    if (c->ws != nullptr) {
+    if (tables) {
+        blocks = spread_units(blocks, b.lats, b.nrhs);
+        mblocks = spread_units(mblocks, b.lats, b.nrhs);
+        rblocks = spread_units(rblocks, b.lats, b.nrhs);
         // launches already queued may still read the old tables
         HIPCHK(hipDeviceSynchronize());
         HIPCHK(hipMemcpy(b.units[pi], units.data(), sizeof(UnitDesc) * units.size(), hipMemcpyHostToDevice));
@@ -3771,7 +3779,7 @@ int hmc_batch_create(int nchains, const int* L, const int* L_tau, const double* 
         TuneChoice ch;
         if (tune_cache_lookup(tune_key(c), ch)) apply_choice(c, ch);
     }
-    (void)upload_batch_shape(c, 0, c->bpr64);    // counts only until the workspace is set
+    (void)upload_batch_shape(c, 0, c->bpr64);
     (void)upload_batch_shape(c, 1, c->bpr32);
     c->need = ws_layout(c, nullptr);
     c->graphs = true;
