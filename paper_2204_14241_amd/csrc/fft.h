@@ -32,7 +32,7 @@
 // table, and small slices share a workgroup (slice_cut in hmc.hip).  Per pass, before -> after:
 // FP32 80 x 80 x 200 33.4 -> 25.5 us; FP32 16 x 16 x 80, four vectors, 14.0 -> 6.2 us; FP64 28 x 28 x 75, two
 // vectors, 28.2 -> 9.7 us; FP64 60 x 60 x 160 41.9 -> 24.4 us; FP32, twelve chains of 12 to 48, four
-// vectors each, all running, 172 -> 56 us.  Loading the first butterfly's inputs before the record is
+// vectors each, all running, 171 -> 58 us.  Loading the first butterfly's inputs before the record is
 // reduced gained nothing (28.3 us at 80 x 80 x 200: the registers cost a workgroup per CU), nor did 256-
 // and 384-thread workgroups (33 and 30 us).
 #pragma once
@@ -49,8 +49,8 @@ namespace hmc {
 constexpr int kFftMaxStages = 12;   // 4^12 > any lattice extent accepted
 constexpr int kFftMaxRadix = 16;
 // Largest radix of the kernels' narrower instantiation: every L up to 80 with two stages needs no
-// more, and radices 12, 14 and 16 raise the slice passes from 57 to 76 registers in FP32 and from
-// 87 to 123 in FP64 (60 x 60 x 160: 24.4 us against 25.2).
+// more, and radices 12, 14 and 16 raise the slice passes from 46-49 to 64-72 registers in FP32 and
+// from 73-79 to 105-121 in FP64 (60 x 60 x 160: 24.4 us against 25.2).
 constexpr int kFftNarrow = 10;
 
 // n / d by a 32-bit reciprocal: m = floor((2^32 - 1) / d) + 1 = (2^32 + e) / d with 0 <= e < d, so
